@@ -157,44 +157,206 @@ __global__ void k_query_reset(unsigned long long *app_count, int32_t *order_flag
 //
 // First hit of each ray: among the primitives it meets, the one with the
 // smallest entry parameter, ties to the smallest leaf position (Morton
-// order).  One lane walks Alg. 1 from the root and enters a node only if the
-// ray meets its box with an entry parameter below the best hit so far (any
-// entry while there is none).  A box inside a node's box never has a smaller
-// entry parameter (the slab test is monotone under box inclusion), so a
-// pruned subtree holds no better hit; Alg. 1 reaches leaves in ascending
-// position, so on equal entries the first leaf found stays.  An n = 0 tree
-// gives every ray hit -1 and t = +inf (n = 0 never reaches here: the caller
-// fills those).
-__global__ __launch_bounds__(kBlock) void k_ray_first(Tree tr, const float *__restrict__ rays, int m,
-                                                      int32_t *__restrict__ hit, float *__restrict__ t)
+// order).  One lane per ray goes down from the root, the nearer child first,
+// so that a close hit is found early and prunes what is behind it.  A node
+// with the leaf range [l, r] and the split g has the children g and g + 1
+// (leaves where the range ends there), so one step loads and tests both:
+// usually neighbouring records.  The farther child waits on a stack.  A node
+// is entered only if it can hold a better hit: an entry below the best one,
+// or an equal one and leaves before the best hit's (a box inside a node's
+// box never has a smaller entry parameter: the slab test is monotone under
+// box inclusion).  The best hit is unique, so the order of the visits does
+// not show.  An n = 0 tree gives every ray hit -1 and t = +inf (n = 0 never
+// reaches here: the caller fills those).
+//
+// Bound by the latency of its scattered loads and then by its vector
+// instructions, so what counts is waves per CU: the first kRayStack stack
+// entries lie in LDS and the rest, rarely reached, in the call's workspace
+// (2^20 rays on 2^24 clustered boxes: 0.96 ms with 6 entries in LDS, 1.04
+// with 8, 1.00 with 10).  A wave owns `share` rays; a lane whose ray is done takes the
+// next one, kRayRefill lanes at a time (1.02 ms without).  One walk in
+// preorder along the ropes per ray took 11.3 ms: it visits the children in
+// index order, so most of what it visits lies behind the hit.
+constexpr int kRayBlock = 64;
+constexpr int kRayStack = 6;
+constexpr int kRayRefill = 8;
+constexpr int kRayWaves = 6144;   // give waves more than 64 rays only above this many waves
+// stack entries a walk can need: one per level of the tree, whose path has
+// strictly falling delta* ranks (63 code bits and 30 index bits at most)
+constexpr int kRayDepth = 96;
+
+// The slab test of Ray::enter with the hardware's minimum and maximum.  Its
+// verdict is the same and its entry parameter equal (a zero may differ in
+// sign) for a ray whose origin, direction and interval hold no NaN, none of
+// whose axes is parallel, and whose direction is finite: then no product is
+// NaN.  Other rays take Ray::enter.
+struct FastRay {
+    float o[3], inv[3], tmin, tmax;
+    __device__ bool set(const Ray &q)
+    {
+        bool ok = q.tmin == q.tmin && q.tmax == q.tmax;
+        tmin = q.tmin;
+        tmax = q.tmax;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            o[k] = q.o[k];
+            inv[k] = q.inv[k];
+            ok = ok && !q.par[k] && fabsf(q.o[k]) < INFINITY && fabsf(q.d[k]) < INFINITY;
+        }
+        return ok;
+    }
+    __device__ bool enter(float4 lo, float4 hi, float *e) const
+    {
+        const float ax = (lo.x - o[0]) * inv[0], bx = (hi.x - o[0]) * inv[0];
+        const float ay = (lo.y - o[1]) * inv[1], by = (hi.y - o[1]) * inv[1];
+        const float az = (lo.z - o[2]) * inv[2], bz = (hi.z - o[2]) * inv[2];
+        const float in = fmaxf(fmaxf(fmaxf(fminf(ax, bx), fminf(ay, by)), fminf(az, bz)), tmin);
+        const float out = fminf(fminf(fminf(fmaxf(ax, bx), fmaxf(ay, by)), fmaxf(az, bz)), tmax);
+        *e = in;
+        return in <= out;
+    }
+};
+
+struct FirstHit {
+    float best;
+    int pos;   // leaf position of the best hit (-1: none)
+    __device__ bool better(float e, int l) const
+    {
+        return pos < 0 || e < best || (e == best && l < pos);
+    }
+};
+
+__global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *__restrict__ rays, int m,
+                                                         int share, int32_t *__restrict__ hit,
+                                                         float *__restrict__ t, int2 *__restrict__ deep)
 {
-    const int leaf0 = tr.leaf0();
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < m; j += stride) {
-        Ray q;
-        q.load(rays, (int)j);
-        int best_hit = -1, v = 0;
-        float best = INFINITY;
-        int64_t budget = tr.walk_budget();
-        while (v != -1 && --budget >= 0) {
-            float4 a, b;
-            tr.load(v, a, b);
-            float e;
-            if (q.enter(a, b, &e) && (best_hit < 0 || e < best)) {
-                if (v >= leaf0) {
-                    best_hit = __float_as_int(a.w);
-                    best = e;
-                    v = __float_as_int(b.w);
+    __shared__ int2 s_stack[kRayStack][kRayBlock];    // node, other end of its range
+    __shared__ float s_enter[kRayStack][kRayBlock];   // its entry parameter
+    const int leaf0 = tr.leaf0(), tid = threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kRayBlock;
+    deep += (int64_t)blockIdx.x * kRayBlock + tid;
+    auto split_of = [&](int c) { return c >= leaf0 ? c - leaf0 : c; };
+    float4 root_a, root_b;
+    tr.load(0, root_a, root_b);
+    const int root_g = split_of(__float_as_int(root_a.w));
+    // this wave's rays not taken yet
+    int64_t next = (int64_t)blockIdx.x * share;
+    const int64_t end = next + share < m ? next + share : m;
+    int j = -1, l = 0, r = 0, g = 0, sp = 0;
+    int64_t budget = 0;
+    FastRay q;
+    bool fast = true;
+    FirstHit f{INFINITY, -1};
+    while (true) {
+        const uint64_t idle = __ballot(j < 0);
+        if (idle != 0 && next < end && (__popcll(idle) >= kRayRefill || idle == ~0ull)) {
+            const int64_t mine = next + lanes_below(idle);
+            next += __popcll(idle);
+            if (j < 0 && mine < end) {
+                Ray x;
+                x.load(rays, (int)mine);
+                fast = q.set(x);
+                f = FirstHit{INFINITY, -1};
+                budget = tr.walk_budget();
+                sp = 0;
+                l = 0;
+                r = tr.n - 1;
+                g = root_g;
+                float e;
+                const bool met = x.enter(root_a, root_b, &e);
+                if (met && leaf0 > 0) {
+                    j = (int)mine;
                 } else {
-                    v = __float_as_int(a.w);
+                    hit[mine] = met ? __float_as_int(root_a.w) : -1;
+                    t[mine] = met ? e : INFINITY;
                 }
+            }
+            continue;
+        }
+        if (idle == ~0ull) break;
+        if (j >= 0) {
+            const bool lleaf = g == l, rleaf = g + 1 == r;
+            float4 la, lb, ra, rb;
+            tr.load(lleaf ? leaf0 + g : g, la, lb);
+            tr.load(rleaf ? leaf0 + r : g + 1, ra, rb);
+            float el, er;
+            bool hl, hr;
+            if (__ballot(!fast) == 0) {
+                hl = q.enter(la, lb, &el);
+                hr = q.enter(ra, rb, &er);
             } else {
-                v = __float_as_int(b.w);
+                Ray x;
+                x.load(rays, j);
+                hl = x.enter(la, lb, &el);
+                hr = x.enter(ra, rb, &er);
+            }
+            hl = hl && f.better(el, l);
+            if (hl && lleaf) f = FirstHit{el, l};
+            hr = hr && f.better(er, g + 1);
+            if (hr && rleaf) f = FirstHit{er, r};
+            hl = hl && !lleaf && f.better(el, l);
+            hr = hr && !rleaf;
+            const int gl = split_of(__float_as_int(la.w)), gr = split_of(__float_as_int(ra.w));
+            const bool lnear = hl && (!hr || el <= er);
+            if (hl && hr) {
+                const int2 far = lnear ? make_int2(g + 1, r) : make_int2(g, l);
+                const float fe = lnear ? er : el;
+                if (sp < kRayStack) {
+                    s_stack[sp][tid] = far;
+                    s_enter[sp][tid] = fe;
+                } else {
+                    deep[(sp - kRayStack) * stride] = far;
+                }
+                ++sp;
+            }
+            bool go = hl || hr;
+            l = lnear ? l : g + 1;
+            r = lnear ? g : r;
+            g = lnear ? gl : gr;
+            if (!go) {
+                int2 s = make_int2(0, 0);
+                while (!go && sp > 0) {
+                    --sp;
+                    float e;
+                    if (sp < kRayStack) {
+                        s = s_stack[sp][tid];
+                        e = s_enter[sp][tid];
+                    } else {   // its entry parameter is computed again
+                        s = deep[(sp - kRayStack) * stride];
+                        Ray x;
+                        x.load(rays, j);
+                        float4 a, b;
+                        tr.load(s.x, a, b);
+                        x.enter(a, b, &e);
+                    }
+                    l = s.x < s.y ? s.x : s.y;
+                    go = f.better(e, l);
+                }
+                if (go) {
+                    r = s.x < s.y ? s.y : s.x;
+                    g = split_of(__float_as_int(tr.nodes[2 * (int64_t)s.x].w));
+                }
+            }
+            if (--budget < 0 && go) {
+                tr.budget_spent();
+                go = false;
+            }
+            if (!go) {
+                int prim = -1;
+                float best = INFINITY;
+                if (f.pos >= 0) {   // the entry parameter exactly as the test defines it
+                    Ray x;
+                    x.load(rays, j);
+                    float4 a, b;
+                    tr.load(leaf0 + f.pos, a, b);
+                    x.enter(a, b, &best);
+                    prim = __float_as_int(a.w);
+                }
+                hit[j] = prim;
+                t[j] = best;
+                j = -1;
             }
         }
-        if (budget < 0) tr.budget_spent();
-        hit[j] = best_hit;
-        t[j] = best;
     }
 }
 
@@ -431,7 +593,14 @@ hipError_t launch_ray_first(const lbvh_node *nodes, int n, const float *rays, in
     prof_begin(K_QCOUNT, s);
     hipLaunchKernelGGL(k_query_reset, dim3(1), dim3(kBlock), 0, s, S.app_count, S.order_flag, 0,
                        S.sort_ctr, S.qhist, S.err, nullptr, (int64_t)0);
-    hipLaunchKernelGGL(k_ray_first, dim3(grid_for(m)), dim3(kBlock), 0, s, tr, rays, m, hit, t);
+    const int share = kRayBlock * std::max(1, m / (kRayBlock * kRayWaves));
+    const int64_t waves = ((int64_t)m + share - 1) / share;
+    // the deep stacks take the workspace up to the control words: about 800
+    // bytes a query and more than 250 KiB, of which (96 - 6) * 8 are used
+    if ((size_t)waves * kRayBlock * (kRayDepth - kRayStack) * sizeof(int2) > L.ctrl)
+        return hipErrorInvalidValue;   // not expected
+    hipLaunchKernelGGL(k_ray_first, dim3((unsigned)waves), dim3(kRayBlock), 0, s, tr, rays, m, share, hit,
+                       t, reinterpret_cast<int2 *>(ws));
     prof_end(K_QCOUNT, s);
     return hipGetLastError();
 }

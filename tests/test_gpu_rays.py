@@ -200,3 +200,33 @@ def test_first_hit_error_word(ws):
         lb.lbvh_tune("query_walk_budget", old)
     lb.query_first(tree, rays, workspace=qws)
     lb.check_query(qws, 64)
+
+
+@pytest.mark.parametrize("n,m", [(2, 63), (3, 65), (40, 786500), (3000, 700), (20000, 4097)])
+def test_first_hit_nearer_child_first(n, m, ws):
+    """The nearer-child-first walk: rays that start inside many boxes (all
+    entries equal: the first position wins), equal boxes, rays with infinite,
+    zero and NaN components among ordinary ones, stacks deeper than the
+    entries kept on chip, and more rays than one per lane of the grid."""
+    rng = np.random.default_rng([47, n])
+    c = rng.random((n, 3)) * 0.2 + 0.4
+    half = np.where(np.arange(n)[:, None] % 3 == 0, 0.3, 0.02) * rng.random((n, 3))
+    boxes = np.concatenate([c - half, c + half], 1).astype(np.float32)
+    boxes[n // 2:] = boxes[: n - n // 2]          # every box twice
+    rays = workloads.rays_toward(rng.random((m, 3), dtype=np.float32) * np.float32(0.2) + np.float32(0.4), rng)
+    k = np.arange(m)
+    rays[k % 4 == 1, :3] = 0.5                    # from the middle of the boxes
+    rays[k % 7 == 2, 3] = np.float32(0.125)
+    rays[k % 11 == 3, 7] = 1.0
+    rays[k % 13 == 4, 4 + n % 3] = 0.0
+    rays[k % 101 == 5, 5] = np.inf
+    rays[k % 103 == 6, 4] = np.nan
+    rays[k % 107 == 7, 3] = -np.inf
+    rays[k % 109 == 8, 1] = -np.inf
+    rays[k % 113 == 9, 7] = np.nan
+    for bits in (30, 63):
+        ref = oracle.build(1, boxes, bits)
+        tree, _ = gpu_build(boxes, 1, bits, ws)
+        rhit, rt, _ = oracle.ray_first_traverse(rays, ref)
+        hit, t = gpu_first(tree, rays, ws)
+        assert_first_equal(hit, t, rhit, rt)
