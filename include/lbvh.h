@@ -177,13 +177,10 @@ int64_t lbvh_query_workspace_bytes(int64_t m);
  * (dx*dx + dy*dy) + dz*dz <= r*r in binary32 (closed ball, no fused
  * multiply-add).  Box j is lohi[j] = (lo.xyz, hi.xyz): B matches if
  * lo <= B.hi and B.lo <= hi on every axis (closed boxes).
- * Each query's walk is run as independent pieces over aligned blocks of
- * leaves (same nodes, same order); the pieces, a hit mask per piece and
- * the hit offsets are kept in the workspace for the fill call, which tests
- * no box again for pieces of at most 256 leaves.  With the "query_order"
- * knob the walks run in a Morton order of the queries; the workspace then
- * also keeps the reordered queries and each one's shift to its output
- * slot.
+ * The queries are walked in packets by whole waves (the same leaves, in the
+ * same order); each query's first hits and the places of the others are kept
+ * in the workspace for the fill call.  Many queries (32768 and more, or with
+ * the "query_order" knob) are walked in a Morton order of theirs.
  *   xyzr / lohi : device, float [m][4] / [m][6], 16-byte aligned.
  *   offsets     : device int64 [m+1]; receives the CSR offsets,
  *                 offsets[0] = 0 and offsets[m] = total number of hits.
@@ -394,25 +391,20 @@ const char *lbvh_last_hip_error(void);
  *       2 = 1024 x 8, 3 = 512 x 16 (a block whose tables do not fit the LDS
  *       runs as 256 x 16).  Mode 1 applies to batches whose largest scene
  *       has at most 262144 primitives; larger batches run mode 0.
- *   "query_split1", "query_split2": the single-tree count call cuts each
- *       query's Alg. 1 walk into pieces at aligned blocks of 2^split1
- *       leaves, then cuts those at blocks of 2^split2 leaves, and walks the
- *       pieces in parallel; values 2 .. 24 (defaults 12 and 7).  The fill
- *       call reuses the count call's pieces.
- *   "query_leaf_mode": how the single-tree count and fill calls handle the
- *       finest pieces: 0 = one wave tests a piece's leaves 64 at a time
- *       (default; best when queries hit many leaves), 1 = pieces whose
- *       start-node box lies mostly outside the query are walked with Alg. 1
- *       by one lane, the rest as in 0 (best for sparse queries).  Both
- *       record the same per-piece hit masks, and the fill call reads those
- *       whatever the knobs are when it is enqueued.
+ *   "query_split1": the rest of a heavy packet of queries is cut into tasks of
+ *       at most 2^(split1 - 7) leaves per query of the packet, at least 512;
+ *       values 2 .. 24 (default 12: 2048 leaves for a packet of 64).
+ *   "query_split2": how long a packet walks before its rest may be cut: about
+ *       2^(split2 - 3) times 3 steps; values 2 .. 24 (default 7: 48).
+ *   "query_leaf_mode": 0 = tasks of that width (default), 1 = four times wider.
  *   "query_order": 1 = the single-tree count call first sorts the queries
  *       by a 16-bit Morton key of their centres (in the root's box) and
- *       walks them in that order, so that neighbouring threads walk
- *       neighbouring parts of the tree; offsets and indices still come out
- *       in the caller's query order.  0 = the caller's order (default).
- *       The count call records which it did in the workspace, and the fill
- *       call follows that whatever the knob is when it is enqueued.
+ *       walks them in that order, so that the queries of a packet walk
+ *       the same part of the tree; offsets and indices still come out
+ *       in the caller's query order.  0 = only for 32768 queries and more,
+ *       which share packets (default).  The count call records which it did
+ *       in the workspace, and the fill call follows that whatever the knob
+ *       is when it is enqueued.
  *   "query_walk_budget": for tests of the error path: caps the node visits
  *       of each walk of a count call (0 = no cap beyond 2n, the default).
  *       A walk that hits the cap stops; lbvh_query_check then reports it.
@@ -439,8 +431,7 @@ int64_t lbvh_tune(const char *name, int64_t value);
  * launches since the last reset.  Names: "bounds", "bounds_final",
  * "morton", "sort_pass", "bottomup" (level 0 of the bottom-up pass),
  * "bottomup_up" (its upper levels), "batch_prep" (batched plan and
- * per-scene codes), "query_order" (the query sort and the mapping back to
- * the caller's order), "query_split",
+ * per-scene codes), "query_order" (the query sort), "query_split",
  * "query_count", "query_fill", "scan" (scans and offset bookkeeping).
  * Returns LBVH_EINVAL for an unknown name. */
 int lbvh_profile_enable(int32_t on);

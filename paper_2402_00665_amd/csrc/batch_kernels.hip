@@ -576,10 +576,17 @@ __global__ __launch_bounds__(kBlock) void k_batch_count(const float4 *__restrict
     counts[j] = cnt;
 }
 
-// Start of a batched count call: clear its error word.
-__global__ void k_batch_query_reset(uint32_t *err)
+// Start of a batched count call: clear its error word, the scan's tile
+// counter and its status words.
+__global__ __launch_bounds__(kBlock) void k_batch_query_reset(uint32_t *err, uint32_t *counter,
+                                                              uint64_t *status, int64_t words)
 {
-    if (threadIdx.x == 0) *err = 0u;
+    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (j == 0) {
+        *err = 0u;
+        *counter = 0u;
+    }
+    if (j < words) status[j] = 0ull;
 }
 
 template <class Q>
@@ -840,17 +847,19 @@ hipError_t run_batch_query(const lbvh_batch *b, const float *q, const int64_t *q
         prof_end(K_QFILL, s);
         return hipGetLastError();
     }
-    int32_t *counts = reinterpret_cast<int32_t *>(ws + L.cnt1);
-    int64_t *partials = reinterpret_cast<int64_t *>(ws + L.partials);
+    int32_t *counts = reinterpret_cast<int32_t *>(ws + L.counts);
+    uint64_t *status = reinterpret_cast<uint64_t *>(ws + L.scan_status);
+    uint32_t *counter = reinterpret_cast<uint32_t *>(ws + L.ctrl);
     uint32_t *err = reinterpret_cast<uint32_t *>(ws + L.ctrl + kQueryErrorByte);
     prof_begin(K_QCOUNT, s);
-    hipLaunchKernelGGL(k_batch_query_reset, dim3(1), dim3(64), 0, s, err);
+    hipLaunchKernelGGL(k_batch_query_reset, dim3((unsigned)((scan_tiles(m) + kBlock - 1) / kBlock)), dim3(kBlock),
+                       0, s, err, counter, status, scan_tiles(m));
     hipLaunchKernelGGL((k_batch_count<Q>), dim3(g), dim3(kBlock), 0, s, nodes, b->leaf_perm,
                        b->seg_off, qseg_off, b->num_scenes, q, m, counts, cache, err,
                        tune_get(TUNE_QBUDGET));
     prof_end(K_QCOUNT, s);
     prof_begin(K_SCAN, s);
-    scan(counts, m, nullptr, partials, offsets, s);
+    scan(counts, m, status, counter, offsets, nullptr, err, s);
     prof_end(K_SCAN, s);
     return hipGetLastError();
 }

@@ -42,42 +42,43 @@ BuildLayout build_layout(int64_t n, int code_bits)
 QueryLayout query_layout(int64_t m)
 {
     QueryLayout L{};
-    L.cap1 = 2 * m + 1024;
-    L.cap2 = 6 * m + 4096;
-    L.out1 = L.cap1 + m;        // an unsplit query adds one piece
-    L.out2 = L.cap2 + L.out1;   // an unsplit level-1 piece adds one
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t at = off; off = align256(off + bytes); return at; };
-    L.cnt1 = take((size_t)(m + 1) * sizeof(int32_t));
-    L.off1 = take((size_t)(m + 1) * sizeof(int64_t));
-    L.items1 = take((size_t)L.out1 * 16);
-    L.cnt2 = take((size_t)L.out1 * sizeof(int32_t));
-    L.off2 = take((size_t)(L.out1 + 1) * sizeof(int64_t));
-    L.items2 = take((size_t)L.out2 * 16);
-    L.app_piece = take((size_t)L.cap2 * 16);   // shared by both levels (cap2 >= cap1)
-    L.app_item = take((size_t)L.cap2 * sizeof(int64_t));
-    L.app_rank = take((size_t)L.cap2 * sizeof(int32_t));
-    L.hcnt = take((size_t)L.out2 * sizeof(int32_t));
-    L.hmask = take((size_t)L.out2 * kMaskWords * sizeof(uint64_t));
-    L.hoff = take((size_t)(L.out2 + 1) * sizeof(int64_t));
-    L.partials = take((size_t)((L.out2 + kScanTile - 1) / kScanTile + 1) * sizeof(int64_t));
+    const size_t mm = (size_t)m;
+    L.light = take(mm * sizeof(int32_t));
+    L.counts = take(mm * sizeof(int32_t));
+    L.offsets = take((mm + 1) * sizeof(int64_t));
+    L.perm = take(mm * sizeof(int32_t));
+    L.cache = take(mm * kHitCache * sizeof(int32_t));
+    L.packet = packet_size(m);
+    L.packets = (m + L.packet - 1) / L.packet;
+    const size_t packets = (size_t)L.packets;
+    // about 480 bytes a query, at least 32768 tasks
+    L.max_tasks = (uint32_t)std::min<size_t>(32768 + mm * 480 / (32 + 8 * L.packet), 1 << 30);
+    const size_t tasks = L.max_tasks + packets * kOwnTasks;
+    L.resume = take(mm * sizeof(int32_t));
+    L.heavy = take(packets * 32);
+    L.tasks = take(tasks * 32);
+    L.rows = take(tasks * L.packet * sizeof(int32_t));
+    L.places = take(tasks * L.packet * sizeof(int32_t));
+    L.scan_status = take((mm / kScanTile + 1) * sizeof(uint64_t));
+    L.deep = 0;
+    const size_t share = (size_t)ray_share(m), deep_lanes = (mm + share - 1) / share * kRayBlock;
+    off = std::max(off, align256(deep_lanes * (kRayDepth - kRayStack) * 8));
     L.ctrl = take(128);
-    L.qsorted = take((size_t)m * 8 * sizeof(float));   // widest query: a ray
-    L.qperm = take((size_t)m * sizeof(int32_t));
-    L.qoff = take((size_t)(m + 1) * sizeof(int64_t));
     L.total = off;
-    // the query-order sort's buffers live in `hmask`, which is first
-    // written by the leaf level, after the sort is done with them
-    const size_t qtiles = (size_t)((m + kQOrderTile - 1) / kQOrderTile);
-    size_t q = L.hmask;
+    // the query-order sort's buffers live in `cache`, which is first
+    // written by the walks, after the sort is done with them (for few
+    // queries, also in what follows it: the heavy packets' records)
+    const size_t qtiles = (mm + kQOrderTile - 1) / kQOrderTile;
+    size_t q = L.cache;
     auto inner = [&](size_t bytes) { size_t at = q; q = align256(q + bytes); return at; };
-    L.qkeys[0] = inner((size_t)m * sizeof(uint32_t));
-    L.qkeys[1] = inner((size_t)m * sizeof(uint32_t));
-    L.qvals = inner((size_t)m * sizeof(int32_t));
+    L.qkeys[0] = inner(mm * sizeof(uint32_t));
+    L.qkeys[1] = inner(mm * sizeof(uint32_t));
+    L.qvals = inner(mm * sizeof(int32_t));
     L.qstatus[0] = inner(qtiles * kRadix * sizeof(uint32_t));
     L.qstatus[1] = inner(qtiles * kRadix * sizeof(uint32_t));
     L.qhist = inner((size_t)kQOrderPasses * kRadix * sizeof(uint32_t));
-    // hmask holds 32 * out2 >= 288 m + 163840 bytes: more than the above
     return L;
 }
 
@@ -86,9 +87,9 @@ QueryLayout batch_query_layout(int64_t m)
     QueryLayout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t at = off; off = align256(off + bytes); return at; };
-    L.cnt1 = take((size_t)(m + 1) * sizeof(int32_t));
+    L.counts = take((size_t)(m + 1) * sizeof(int32_t));
     L.hcache = take((size_t)m * 64 * sizeof(int32_t));   // first 64 hits of each query
-    L.partials = take((size_t)((m + kScanTile - 1) / kScanTile + 1) * sizeof(int64_t));
+    L.scan_status = take((size_t)((m + kScanTile - 1) / kScanTile + 1) * sizeof(uint64_t));
     L.ctrl = take(128);
     L.total = off;
     return L;

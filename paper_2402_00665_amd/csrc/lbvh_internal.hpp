@@ -26,15 +26,26 @@ constexpr int kFanout = 256;          // level-(L-1) blocks per level-L block
 constexpr int kBUThreads = 2 * kFanout;  // one thread per handed-over climb
 constexpr int kClimbBytes = 48;       // a climb handed between bottom-up levels
 constexpr int kMaxBatchLevels = 3;    // kChunk * kFanout^3 >= LBVH_MAX_PRIMS
+// first-hit walks: lanes of a block, waves above which a wave gets more
+// than 64 rays, stack entries on chip and in all (one per level of the tree,
+// whose paths have strictly falling delta* ranks: 63 code bits and 30 index
+// bits at most)
+constexpr int kRayBlock = 64;
+constexpr int kRayWaves = 6144;
+constexpr int kRayStack = 6;
+constexpr int kRayDepth = 96;
 constexpr int kScanItems = 8;         // values per thread in the query scan
-constexpr int kSplit1 = 12;           // default: query walks cut by aligned blocks of 2^12 leaves
-constexpr int kSplit2 = 7;            // default: ... then by blocks of 2^7 leaves
+constexpr int kSplit1 = 12;           // defaults of the knobs query_split1 (leaves of a task)
+constexpr int kSplit2 = 7;            // ... and query_split2 (steps before a packet is cut)
 constexpr int kQueryGridMax = 8192;   // blocks of the grid-stride query kernels
+constexpr int kCutGrid = 1024;          // most blocks of the kernel over heavy packets
+constexpr int kOwnTasks = 8;            // places for tasks that every packet has of its own
+constexpr int kTaskGrid = 16384;        // ... of the kernels over their tasks
+constexpr int kQOrderMin = 32768;     // queries from which they are sorted and share packets
 constexpr int kQOrderTile = 2048;     // keys per tile of the query-order sort (512 x 4)
 constexpr int kQOrderPasses = 2;      // 16-bit query-order keys: two 8-bit digits
 constexpr int kQOrderKeyBlocks = 256;  // blocks of the query-order key kernel
-constexpr int kMaskLeaves = 256;     // widest level-2 piece that gets a leaf-hit mask
-constexpr int kMaskWords = kMaskLeaves / 64;
+constexpr int kHitCache = 32;        // light-walk hits of a query kept for the fill
 constexpr int kScanTile = kBlock * kScanItems;
 
 // the error word of a query call: byte offset in the query workspace's ctrl
@@ -106,35 +117,45 @@ struct BuildLayout {
 BuildLayout build_layout(int64_t n, int code_bits);
 
 struct QueryLayout {
-    int64_t cap1, cap2;  // capacities of the level-1 and level-2 append lists
-    int64_t out1, out2;  // pieces each level can emit: its list plus one per unsplit item
-    size_t cnt1;       // m int32: level-1 pieces per query
-    size_t off1;       // m+1 int64
-    size_t items1;     // out1 int4 (query, node, left bound, range end)
-    size_t cnt2;       // out1 int32: level-2 pieces per level-1 piece
-    size_t off2;       // out1+1 int64
-    size_t items2;     // out2 int4
-    size_t app_piece;  // cap2 int4: pieces appended by a split level's count pass
-    size_t app_item;   // cap2 int64: ... the item each came from
-    size_t app_rank;   // cap2 int32: ... and its rank among that item's pieces
-    size_t hcnt;       // out2 int32: hits per level-2 piece
-    size_t hmask;      // out2 x kMaskWords uint64: leaf-hit mask of each level-2 piece
-    size_t hcache;     // batched: m x 64 int32, each query's first hits
-    size_t hoff;       // out2+1 int64
-    size_t partials;   // scan tile sums
-    size_t ctrl;       // overflow flags, piece counts, query-order flag, sort counters, error word
-    // query order (single tree): the reordered copy of the queries, each
-    // reordered position's caller index, and the offsets in reordered order
-    size_t qsorted;    // m x 8 float (the widest query, a ray)
-    size_t qperm;      // m int32
-    size_t qoff;       // m+1 int64
-    // the order's radix sort, inside `hmask` (unused until the leaf level)
+    // single tree: per query
+    size_t light;      // m int32: hits of the query's light walk
+    size_t counts;     // m int32: all its hits (batched too)
+    size_t offsets;    // m+1 int64: the caller's offsets, for the fill call
+    size_t cache;      // m x kHitCache int32: the light walks' first hits
+    size_t perm;       // m int32: the order the queries are walked in
+    int packet;        // queries of a packet
+    int64_t packets;
+    // heavy packets
+    size_t resume;     // m int32: first leaf of the rest of a heavy packet's query
+    size_t heavy;      // packets x 32 bytes
+    uint32_t max_tasks; // the pool of tasks; then kOwnTasks a packet
+    size_t tasks;      // (max_tasks + kOwnTasks packets) x 32 bytes
+    size_t rows;       // (the same) x packet int32: hits of each task's queries
+    size_t places;     // the same: their places among the queries' hits
+    // the query order's radix sort, inside `cache` (unused until the walks)
     size_t qkeys[2];   // m uint32 each
     size_t qvals;      // m int32 (first pass's values)
     size_t qstatus[2]; // qtiles x kRadix uint32 each
     size_t qhist;      // 2 x kRadix uint32
+    size_t scan_status; // scan tiles uint64 (batched too)
+    size_t hcache;     // batched: m x 64 int32, each query's first hits
+    size_t deep;       // first hits: the walks' deep stacks, in place of all of the above
+    size_t ctrl;       // control words (batched too)
     size_t total;
 };
+
+// Queries of a packet: one until there are kQOrderMin of them, then as many as
+// leave kPacketWaves packets, twice the waves that fill the machine's SIMDs
+// four deep (16384 or 32768: the same or slower on 2^20 queries).
+constexpr int kPacketWaves = 8192;
+inline int packet_size(int64_t m)
+{
+    int p = 1;
+    while (m >= kQOrderMin && p < 64 && p * (int64_t)kPacketWaves < m) p *= 2;
+    return p;
+}
+
+inline int ray_share(int64_t m) { return (int)(kRayBlock * std::max<int64_t>(1, m / (kRayBlock * kRayWaves))); }
 
 QueryLayout query_layout(int64_t m);
 QueryLayout batch_query_layout(int64_t m);   // counts, first hits, scan sums
