@@ -626,11 +626,37 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(const float4 *__restrict_
 struct BatchSortShape { int threads, items; };
 constexpr BatchSortShape kBatchShapes[] = {{256, 16}, {256, 8}, {512, 8}, {512, 16}};
 
-int batch_sort_variant(int bits)
+// How a batch of N primitives in scenes of at most max_scene is sorted: one
+// block per scene or segmented passes, digit width, shape.  The knobs' choice,
+// unless mode, shape and width stand at their defaults.  Then one block per
+// scene where it sorts a scene on chip (up to a tile of 4096), or where there
+// are so many scenes that the largest block, alone with max_scene keys, is not
+// what takes the time (us of whole 63-bit builds, block against segmented:
+// 64 scenes up to 4000: 70 / 105, 4096 up to 65536 (537 times the largest):
+// 2551 / 3942, 300 up to 250000 (157 times): 3854 / 4168, but 512 up to 65536
+// (55 times): 727 / 568).  Blocks of 512 x 8, or 1024 x 8 where scenes exceed
+// 65536; segmented passes of 512 x 8 and 10 or 9 bits (568 against 596 us on
+// those 512 scenes with 256 x 16).
+struct BatchPlan { bool block; int bits, variant; };
+
+BatchPlan batch_plan(int64_t N, int64_t max_scene, int levels, int code_bits)
 {
+    const bool short_codes = code_bits <= 32;
+    // one block per scene only while every scene is small (at most one
+    // upper level: kChunk * kFanout primitives); a block alone on a scene of
+    // millions would set the whole batch's time
+    const bool can = levels <= 1;
+    if (tune_is_default(TUNE_BATCH_SORT_MODE) && tune_is_default(TUNE_BATCH_SORT) &&
+        tune_is_default(short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64)) {
+        if (can && (max_scene <= 4096 || N >= 128 * max_scene))
+            return {true, short_codes ? 8 : 9, max_scene > 65536 ? 2 : 1};
+        return {false, short_codes ? 10 : 9, 2};
+    }
+    const int bits = radix_bits(code_bits);
     const int64_t v = tune_get(TUNE_BATCH_SORT);
     const int var = (v >= 0 && v < 4) ? (int)v : 0;
-    return kBatchShapes[var].threads * kBatchShapes[var].items >= radix_min_tile(bits) ? var : 0;
+    if (can && tune_get(TUNE_BATCH_SORT_MODE) == 1) return {true, bits, var};
+    return {false, bits, kBatchShapes[var].threads * kBatchShapes[var].items >= radix_min_tile(bits) ? var : 0};
 }
 
 template <typename K, int T, int I, int B>
@@ -721,14 +747,14 @@ void launch_scene_sort(const float *prims, const int64_t *seg_off, const int32_t
 template <int KIND, typename K, int B>
 void run_scene_sort(const float *prims, const int64_t *seg_off, const int32_t *order, int S,
                     int code_bits, K *codes, int32_t *leaf_perm, float4 *scene_box, K *keys_alt,
-                    int32_t *vals[2], uint32_t *err, hipStream_t s)
+                    int32_t *vals[2], int shape, uint32_t *err, hipStream_t s)
 {
     const int passes = radix_passes(code_bits, B);
     K *ka = (passes & 1) ? keys_alt : codes;
     K *kb = (passes & 1) ? codes : keys_alt;
     prof_begin(K_SORT, s);
 #define LBVH_SCENE_ARGS prims, seg_off, order, S, code_bits, ka, kb, vals, leaf_perm, scene_box, err, s
-    switch (tune_get(TUNE_BATCH_SORT)) {
+    switch (shape) {
     case 1: launch_scene_sort<KIND, K, B, 512, 8>(LBVH_SCENE_ARGS); break;
     case 2: launch_scene_sort<KIND, K, B, 1024, 8>(LBVH_SCENE_ARGS); break;
     case 3: launch_scene_sort<KIND, K, B, 512, 16>(LBVH_SCENE_ARGS); break;
@@ -739,7 +765,7 @@ void run_scene_sort(const float *prims, const int64_t *seg_off, const int32_t *o
 }
 
 template <int KIND, typename K>
-hipError_t run_batch(const float *prims, const int64_t *seg_off, int S, int64_t N, int levels,
+hipError_t run_batch(const float *prims, const int64_t *seg_off, int S, int64_t N, int64_t max_scene, int levels,
                      int code_bits, lbvh_node *nodes_, K *codes, int32_t *leaf_perm, char *ws,
                      const BatchLayout &L, hipStream_t s)
 {
@@ -757,20 +783,17 @@ hipError_t run_batch(const float *prims, const int64_t *seg_off, int S, int64_t 
     Climb *pend[2] = {reinterpret_cast<Climb *>(ws + L.pend[0]), reinterpret_cast<Climb *>(ws + L.pend[1])};
     float4 *nodes = reinterpret_cast<float4 *>(nodes_);
 
-    const int bits = radix_bits(code_bits);
-    const int variant = batch_sort_variant(bits);
+    const BatchPlan plan = batch_plan(N, max_scene, levels, code_bits);
+    const int bits = plan.bits, variant = plan.variant;
     const int tile = kBatchShapes[variant].threads * kBatchShapes[variant].items;
     int32_t *order = reinterpret_cast<int32_t *>(ws + L.order);
     prof_begin(K_BATCH_PREP, s);
     hipLaunchKernelGGL(k_batch_plan, dim3(1), dim3(kPlanThreads), 0, s, seg_off, S, levels, tile,
                        tile_off, blk_off, ctrl, order);
-    // one block per scene only while every scene is small (at most one
-    // upper level: kChunk * kFanout primitives); a block alone on a scene of millions
-    // would set the whole batch's time
-    if (tune_get(TUNE_BATCH_SORT_MODE) == 1 && levels <= 1) {
+    if (plan.block) {
         prof_end(K_BATCH_PREP, s);
 #define LBVH_SSORT_ARGS prims, seg_off, order, S, code_bits, codes, leaf_perm, scene_box, keys_alt, \
-                        vals, ctrl + kCtrlError, s
+                        vals, variant, ctrl + kCtrlError, s
         if constexpr (sizeof(K) == 4) {
             if (bits == 10) run_scene_sort<KIND, K, 10>(LBVH_SSORT_ARGS);
             else run_scene_sort<KIND, K, 8>(LBVH_SSORT_ARGS);
@@ -874,16 +897,16 @@ hipError_t launch_build_batched(int kind, const float *prims, const lbvh_batch *
     if (b->code_bits == 30) {
         uint32_t *codes = static_cast<uint32_t *>(b->codes);
         if (kind == LBVH_POINTS)
-            return run_batch<LBVH_POINTS, uint32_t>(prims, b->seg_off, S, N, levels, 30, b->nodes,
+            return run_batch<LBVH_POINTS, uint32_t>(prims, b->seg_off, S, N, b->max_scene, levels, 30, b->nodes,
                                                     codes, b->leaf_perm, ws, L, s);
-        return run_batch<LBVH_BOXES, uint32_t>(prims, b->seg_off, S, N, levels, 30, b->nodes, codes,
+        return run_batch<LBVH_BOXES, uint32_t>(prims, b->seg_off, S, N, b->max_scene, levels, 30, b->nodes, codes,
                                                b->leaf_perm, ws, L, s);
     }
     uint64_t *codes = static_cast<uint64_t *>(b->codes);
     if (kind == LBVH_POINTS)
-        return run_batch<LBVH_POINTS, uint64_t>(prims, b->seg_off, S, N, levels, 63, b->nodes, codes,
+        return run_batch<LBVH_POINTS, uint64_t>(prims, b->seg_off, S, N, b->max_scene, levels, 63, b->nodes, codes,
                                                 b->leaf_perm, ws, L, s);
-    return run_batch<LBVH_BOXES, uint64_t>(prims, b->seg_off, S, N, levels, 63, b->nodes, codes,
+    return run_batch<LBVH_BOXES, uint64_t>(prims, b->seg_off, S, N, b->max_scene, levels, 63, b->nodes, codes,
                                            b->leaf_perm, ws, L, s);
 }
 

@@ -163,15 +163,36 @@ constexpr size_t sort_lds_bytes(int key_bytes, int threads, int items, int bits)
            (size_t)threads * items * key_bytes;
 }
 
+// Digit width and tile shape of a build of n primitives: the knobs', unless
+// both stand at their defaults.  Then by size (whole builds of uniform points,
+// us, against 8 bits in 512 x 16 and 9 bits in 768 x 16): small tiles while
+// they do not fill the 256 CUs, so that more blocks share the work, and the
+// largest for large builds, whose tiles then look back less often.
+//   30-bit, 10 bits: 512 x 8    2^14  69 against  88,  2^16  86 / 101
+//                    1024 x 8   2^18 127 / 138,  2^20 191 / 203
+//                    1024 x 16  2^22 373 / 410,  2^24 1149 / 1235 (boxes 1250 / 1333)
+//   63-bit,  9 bits: 512 x 8    2^10  67 / 100,  2^14 109 / 148,  2^18 181 / 214
+//                    1024 x 8   2^20 279 / 296
+//            8 bits: 1024 x 16  2^22 532 / 604,  2^23 918 / 955
+struct SortPlan { int bits, variant; };
+
 template <typename K>
-int sort_variant(int bits)
+SortPlan sort_plan(int64_t n)
 {
-    const int64_t v = tune_get(sizeof(K) == 4 ? TUNE_SORT_VARIANT32 : TUNE_SORT_VARIANT64);
+    constexpr bool short_codes = sizeof(K) == 4;
+    constexpr int bits_knob = short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64;
+    constexpr int shape_knob = short_codes ? TUNE_SORT_VARIANT32 : TUNE_SORT_VARIANT64;
+    if (tune_is_default(bits_knob) && tune_is_default(shape_knob)) {
+        const int variant = n <= (short_codes ? 1 << 17 : 1 << 19) ? 3 : (n <= (1 << 21) ? 5 : 7);
+        return {short_codes ? 10 : (variant == 7 ? 8 : 9), variant};
+    }
+    const int bits = radix_bits(short_codes ? 30 : 63);
+    const int64_t v = tune_get(shape_knob);
     const int var = (v >= 0 && v < kSortShapeCount) ? (int)v : 0;
     const SortShape sh = kSortShapes[var];
     const bool fits = sh.threads * sh.items >= radix_min_tile(bits) &&
                       sort_lds_bytes(sizeof(K), sh.threads, sh.items, bits) <= 150 * 1024;
-    return fits ? var : (sizeof(K) == 4 ? 4 : 3);   // 512 x 16 / 512 x 8 fit every width
+    return {bits, fits ? var : (short_codes ? 4 : 3)};   // 512 x 16 / 512 x 8 fit every width
 }
 
 // One radix pass: the onesweep kernel alone, or (toff given: the
@@ -233,11 +254,10 @@ void launch_onesweep_b(int variant, const K *kin, K *kout, const int32_t *vin, i
 template <int KIND, typename K, int B>
 void run_sort(const float *prims, int n, int code_bits, K *codes, int32_t *leaf_perm,
               const float4 *scene, uint32_t *ctrl, uint32_t *hist, uint32_t *status[2], K *keys_alt,
-              int32_t *vals[2], hipStream_t s)
+              int32_t *vals[2], int variant, hipStream_t s)
 {
     using P = Prims<KIND>;
     const int passes = radix_passes(code_bits, B);
-    const int variant = sort_variant<K>(B);
     const int tile = kSortShapes[variant].threads * kSortShapes[variant].items;
     const int64_t tiles = ((int64_t)n + tile - 1) / tile;
     K *first = (passes & 1) ? keys_alt : codes;
@@ -287,7 +307,8 @@ hipError_t run_build(const float *prims, int n, int code_bits, lbvh_node *nodes_
                         reinterpret_cast<int32_t *>(ws + L.vals[1])};
     int32_t *store = reinterpret_cast<int32_t *>(ws + L.store);
     float4 *nodes = reinterpret_cast<float4 *>(nodes_);
-    const int bits = radix_bits(code_bits);
+    const SortPlan plan = sort_plan<K>(n);
+    const int bits = plan.bits;
 
     const int64_t groups = (int64_t)n / P::G;
     int nb = (int)((groups + 4 * kBlock - 1) / (4 * kBlock));
@@ -303,20 +324,20 @@ hipError_t run_build(const float *prims, int n, int code_bits, lbvh_node *nodes_
     if constexpr (sizeof(K) == 4) {
         if (bits == 10)
             run_sort<KIND, K, 10>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                  keys_alt, vals, s);
+                                  keys_alt, vals, plan.variant, s);
         else
             run_sort<KIND, K, 8>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                 keys_alt, vals, s);
+                                 keys_alt, vals, plan.variant, s);
     } else {
         if (bits == 11)
             run_sort<KIND, K, 11>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                  keys_alt, vals, s);
+                                  keys_alt, vals, plan.variant, s);
         else if (bits == 9)
             run_sort<KIND, K, 9>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                 keys_alt, vals, s);
+                                 keys_alt, vals, plan.variant, s);
         else
             run_sort<KIND, K, 8>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                 keys_alt, vals, s);
+                                 keys_alt, vals, plan.variant, s);
     }
 
     prof_begin(K_BOTTOMUP, s);

@@ -133,11 +133,11 @@ BatchLayout batch_layout(int64_t N, int S, int64_t max_scene, int code_bits)
 // ---------------------------------------------------------------- tuning
 
 namespace {
-// defaults measured on MI355X: 8-bit digits and 512 x 16 tiles for 30-bit
-// keys, 9-bit digits and 768 x 16 tiles for 63-bit keys; the Morton kernel
-// sweeping backwards
+// a digit width and a tile shape that both stand at their defaults leave the
+// choice to the build (sort_plan, batch_plan)
 std::atomic<int64_t> g_tune[TUNE_NUM] = {{4}, {6}, {0}, {kSplit1}, {kSplit2}, {0}, {0}, {8}, {9}, {0},
                                          {1}, {0}, {0}};
+const int64_t kTuneDefault[TUNE_NUM] = {4, 6, 0, kSplit1, kSplit2, 0, 0, 8, 9, 0, 1, 0, 0};
 const char *kTuneNames[TUNE_NUM] = {"sort_variant32", "sort_variant64", "batch_sort_variant",
                                     "query_split1", "query_split2", "query_leaf_mode",
                                     "query_order", "radix_bits32", "radix_bits64",
@@ -148,6 +148,7 @@ const int64_t kTuneMax[TUNE_NUM] = {8, 8, 3, 24, 24, 1, 1, 10, 11, INT32_MAX, 1,
 }  // namespace
 
 int64_t tune_get(int knob) { return g_tune[knob].load(std::memory_order_relaxed); }
+bool tune_is_default(int knob) { return tune_get(knob) == kTuneDefault[knob]; }
 
 int radix_bits(int code_bits)
 {

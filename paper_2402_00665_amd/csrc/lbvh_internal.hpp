@@ -190,6 +190,7 @@ enum TuneKnob {
     TUNE_NUM
 };
 int64_t tune_get(int knob);
+bool tune_is_default(int knob);
 
 // ------------------------------------------------------------ timing
 
