@@ -829,11 +829,13 @@ hipError_t run_batch(const float *prims, const int64_t *seg_off, int S, int64_t 
     if (packed)
         hipLaunchKernelGGL((k_bottomup_l0<KIND, K, true>), dim3((unsigned)L.blocks_max[0]),
                            dim3(kBU0Threads), 0, s, codes, leaf_perm, prims, (int)N, store, nodes,
-                           pend[0], bl, dstar, ctrl + kCtrlError);
+                           pend[0], bl, dstar, N >= kStreamOutMin,
+                           ctrl + kCtrlError);
     else
         hipLaunchKernelGGL((k_bottomup_l0<KIND, K, false>), dim3((unsigned)L.blocks_max[0]),
                            dim3(kBU0Threads), 0, s, codes, leaf_perm, prims, (int)N, store, nodes,
-                           pend[0], bl, dstar, ctrl + kCtrlError);
+                           pend[0], bl, dstar, N >= kStreamOutMin,
+                           ctrl + kCtrlError);
     prof_end(K_BOTTOMUP, s);
     int64_t span = kChunk;
     for (int lv = 1; lv <= levels; ++lv) {

@@ -52,6 +52,19 @@ namespace {
 // records at record 2*seg_off[s].  Level-L blocks of all scenes share one
 // launch; blk_off[s] is the first level-L block of scene s.
 
+// Records of trees beyond the last-level cache (256 MB: 2^22 primitives) are
+// stored past the caches: the levels above read few of them, and the sorted
+// inputs of this pass stay cached instead.  Level 0 on 2^24 boxes 593 -> 573
+// us and its whole build 1162 -> 1106, but 2^20 boxes 286 -> 296, where the
+// levels above still find their records cached.
+constexpr int64_t kStreamOutMin = 1 << 22;
+typedef float Float4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_half(float4 *p, float4 v, bool past_cache)
+{
+    if (past_cache) __builtin_nontemporal_store(Float4{v.x, v.y, v.z, v.w}, reinterpret_cast<Float4 *>(p));
+    else *p = v;
+}
+
 struct BatchLevel {
     const int64_t *seg_off;    // [S+1] scene starts (leaves); nullptr: one tree
     const int32_t *blk_off;    // [S+1] first block of each scene at this level
@@ -100,6 +113,26 @@ __device__ __forceinline__ int park_delta(int32_t v)
     return d == 127 ? 255 : d;
 }
 
+// What a finished node of a chunk still needs beside its box: its split and
+// the right end of its range (relative to the chunk), and whether its left
+// child and its rope are leaves.
+constexpr uint32_t kNoLink = 0xffffffffu;
+static_assert(kChunk <= 1 << 14, "two chunk positions and two flags in a word below kNoLink");
+__device__ __forceinline__ uint32_t pack_link(int split, bool left_leaf, int right, bool rope_leaf)
+{
+    return (uint32_t)split | ((uint32_t)right << 14) | (left_leaf ? 1u << 28 : 0u) |
+           (rope_leaf ? 1u << 29 : 0u);
+}
+__device__ __forceinline__ int link_left(uint32_t v, int A, int leaf0)
+{
+    return A + (int)(v & 0x3fff) + ((v >> 28) & 1 ? leaf0 : 0);
+}
+__device__ __forceinline__ int link_rope(uint32_t v, int A, int n, int leaf0)
+{
+    const int rr = A + (int)((v >> 14) & 0x3fff);
+    return rr == n - 1 ? -1 : rr + 1 + ((v >> 29) & 1 ? leaf0 : 0);
+}
+
 // min and max of two canonical floats (no signalling NaN): the hardware
 // instruction alone.  fminf / fmaxf first quiet both operands (one more
 // instruction each), which the merge loop below does not need: every box in
@@ -118,17 +151,31 @@ __device__ __forceinline__ float max_canon(float a, float b)
     return r;
 }
 
+// The scene of block b: the largest s with off[s] <= b.  Every lane of the
+// wave calls it with the same b: 64 starts are compared at a time, so 4096
+// scenes take two loads in a row where halving takes twelve.
 __device__ __forceinline__ int scene_of(const int32_t *off, int S, int b)
 {
-    int lo = 0, hi = S - 1;   // largest s with off[s] <= b
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (off[mid] <= b) lo = mid;
-        else hi = mid - 1;
+    const int lane = threadIdx.x & 63;
+    int lo = 0, len = S;
+    while (len > 1) {
+        const int step = (len + 63) >> 6;
+        const int at = lane * step;
+        const uint64_t le = __ballot(at < len && off[lo + at] <= b);
+        const int k = le ? __popcll(le) - 1 : 0;   // off never falls: a prefix of the lanes
+        lo += k * step;
+        len = min(step, len - k * step);
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(lo);
 }
 
+// Level 0.  Bound by the gather of the primitives (one line a leaf; 172 us
+// of the 2^23 points' time alone) and by the record stores, which queue in
+// the same L1: so the climb only writes LDS and every record leaves at the
+// end (leaves: at the start) in whole runs, a third of the write requests
+// of storing each as it is finished.  One box slot serves the leaf and the
+// internal node of an index.  us on 2^23 points 309 -> 277, 2^24 clustered
+// boxes 690 -> 573, 4096 scenes (35 M points) 1206 -> 1001.
 template <int KIND, typename K, bool PACKED>
 __global__ __launch_bounds__(kBU0Threads) void k_bottomup_l0(const K *__restrict__ codes_all,
                                                              const int32_t *__restrict__ perm_all,
@@ -137,12 +184,19 @@ __global__ __launch_bounds__(kBU0Threads) void k_bottomup_l0(const K *__restrict
                                                              float4 *__restrict__ nodes_all,
                                                              Climb *__restrict__ pend, BatchLevel bl,
                                                              uint8_t *__restrict__ dstar_all,
-                                                             uint32_t *err)
+                                                             bool past_cache, uint32_t *err)
 {
     __shared__ K s_codes[kChunk + 3];        // codes[A-1 .. B+1]
     __shared__ uint8_t s_delta[kChunk + 2];  // delta*(g) for g in [A-1, B]
     __shared__ int32_t s_store[kChunk];      // store[A .. B-1]
-    __shared__ float s_box[6][2 * kChunk];   // internal A.. then leaves A..
+    // box of leaf A+k until the internal node of that index is written, then
+    // the node's: leaf k is an end of node k's range, so its own parent (node
+    // k itself or a node under it) has read it by then
+    // (rows 32 words apart modulo the banks, three by three, for the copy out)
+    constexpr int kRow = kChunk + 32;
+    __shared__ float s_box[6][kRow];
+    __shared__ uint32_t s_link[kChunk];      // finished internal node: its links
+    __shared__ float4 s_stage[kBU0Threads];  // leaf records on their way out, 32 per wave
     __shared__ Climb s_pend[2];
 
     // this block's chunk: tree (codes, perm, ... of one scene), leaves [A, B)
@@ -171,6 +225,7 @@ __global__ __launch_bounds__(kBU0Threads) void k_bottomup_l0(const K *__restrict
         s_codes[t] = (g >= 0 && g < n) ? codes[g] : (K)0;
     }
     s_store[tid] = -1;
+    s_link[tid] = kNoLink;
     if (tid < 2) s_pend[tid] = empty_climb();
     // this thread's leaf i: primitive id and box (a gather), loaded while
     // the codes arrive
@@ -202,18 +257,34 @@ __global__ __launch_bounds__(kBU0Threads) void k_bottomup_l0(const K *__restrict
         chi[a] = __builtin_canonicalizef(hi[a]);
     }
     if (i < B) {
-        const int sl = kChunk + tid;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) { s_box[a][sl] = clo[a]; s_box[3 + a][sl] = chi[a]; }
+        for (int a = 0; a < 3; ++a) { s_box[a][tid] = clo[a]; s_box[3 + a][tid] = chi[a]; }
     }
     __syncthreads();
     auto delta = [&](int g) -> int { return s_delta[g - A + 1]; };
     // leaf record: the box as given, primitive id, rope (Alg. 2 on the
-    // range [i, i]; delta*(i + 1) is in the table, i + 1 <= B)
+    // range [i, i]; delta*(i + 1) is in the table, i + 1 <= B).  Half a wave's
+    // records at a time turn in LDS so that the wave stores them as one run.
     int rope = -1;
-    if (i < B) {
-        rope = (i == n - 1) ? -1 : (delta(i) < delta(i + 1) ? leaf0 + i + 1 : i + 1);
-        store_node(nodes, leaf0 + i, lo, prim, hi, rope);
+    if (i < B) rope = (i == n - 1) ? -1 : (delta(i) < delta(i + 1) ? leaf0 + i + 1 : i + 1);
+    {
+        const int lane = tid & 63;
+        float4 *stage = s_stage + (tid & ~63);
+        float4 *out = nodes + 2 * (int64_t)(leaf0 + A + (tid & ~63)) + lane;
+        const int left_over = 2 * (cn - (tid & ~63)) - lane;   // halves from this lane's on
+        const float4 r0 = make_float4(lo[0], lo[1], lo[2], __int_as_float(prim));
+        const float4 r1 = make_float4(hi[0], hi[1], hi[2], __int_as_float(rope));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if ((lane >> 5) == h) {
+                stage[2 * (lane & 31)] = r0;
+                stage[2 * (lane & 31) + 1] = r1;
+            }
+            wave_sync();
+            const float4 v = stage[lane];
+            if (left_over > 64 * h) store_half(out + 64 * h, v, past_cache);
+            wave_sync();
+        }
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) { lo[a] = clo[a]; hi[a] = chi[a]; }
@@ -258,11 +329,9 @@ __global__ __launch_bounds__(kBU0Threads) void k_bottomup_l0(const K *__restrict
                         const int dn = delta(is_left ? rr : rl - 1);
                         dr = is_left ? dn : dr;
                         dl = is_left ? dl : dn;
-                        // the sibling: leaf or internal node at split-side
-                        // index sp (selects, not branches); its LDS slot
-                        const int sp = is_left ? p + 1 : p;
-                        const bool sleaf = is_left ? (sp == rr) : (sp == rl);
-                        const int ss = sleaf ? kChunk + (sp - A) : sp - A;
+                        // the sibling: leaf or internal node of the index on
+                        // the split's other side
+                        const int ss = (is_left ? p + 1 : p) - A;
                         // delta*(rr + 1): rr + 1 <= B, in the LDS table (255 at n - 1)
                         const int d_next = delta(rr + 1);
 #pragma unroll
@@ -271,10 +340,9 @@ __global__ __launch_bounds__(kBU0Threads) void k_bottomup_l0(const K *__restrict
                             hi[a] = max_canon(hi[a], s_box[3 + a][ss]);
                         }
                         const int q = dr < dl ? rr : rl;   // Karras index of the parent
-                        const int left = (rl == p) ? leaf0 + p : p;
                         const int qrope = rr == n - 1 ? -1 : (dr < d_next ? leaf0 + rr + 1 : rr + 1);
-                        store_node(nodes, q, lo, left, hi, qrope);
                         const int qs = q - A;
+                        s_link[qs] = pack_link(p - A, rl == p, rr - A, dr < d_next);
 #pragma unroll
                         for (int a = 0; a < 3; ++a) { s_box[a][qs] = lo[a]; s_box[3 + a][qs] = hi[a]; }
                         cur = q;
@@ -289,6 +357,17 @@ __global__ __launch_bounds__(kBU0Threads) void k_bottomup_l0(const K *__restrict
     }
     __syncthreads();
     if (tid < cn) store[A + tid] = s_store[tid];
+    // the chunk's finished internal nodes, as one run of half records
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int h = r * kBU0Threads + tid, k = h >> 1;
+        const uint32_t link = s_link[k];
+        if (link == kNoLink) continue;   // not this chunk's, or finished by a level above
+        const float *row = &s_box[(h & 1) * 3][k];
+        const int w = (h & 1) ? link_rope(link, A, n, leaf0) : link_left(link, A, leaf0);
+        store_half(nodes + 2 * (int64_t)A + h,
+                   make_float4(row[0], row[kRow], row[2 * kRow], __int_as_float(w)), past_cache);
+    }
     if (tid < 2) {
         // field by field: a whole-struct copy around the atomic goes through
         // scratch memory, and scratch in any part of a kernel costs every wave

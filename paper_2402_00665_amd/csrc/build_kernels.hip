@@ -350,10 +350,12 @@ hipError_t run_build(const float *prims, int n, int code_bits, lbvh_node *nodes_
     const bool packed = n <= kPackedMaxN;
     if (packed)
         hipLaunchKernelGGL((k_bottomup_l0<KIND, K, true>), dim3(nbu), dim3(kBU0Threads), 0, s, codes,
-                           leaf_perm, prims, n, store, nodes, pend[0], one, dstar, ctrl + kCtrlError);
+                           leaf_perm, prims, n, store, nodes, pend[0], one, dstar, n >= kStreamOutMin,
+                           ctrl + kCtrlError);
     else
         hipLaunchKernelGGL((k_bottomup_l0<KIND, K, false>), dim3(nbu), dim3(kBU0Threads), 0, s, codes,
-                           leaf_perm, prims, n, store, nodes, pend[0], one, dstar, ctrl + kCtrlError);
+                           leaf_perm, prims, n, store, nodes, pend[0], one, dstar, n >= kStreamOutMin,
+                           ctrl + kCtrlError);
     prof_end(K_BOTTOMUP, s);
     int64_t span = kChunk;
     int in = 0;

@@ -187,5 +187,15 @@ __device__ __forceinline__ void store_node(float4 *nodes, int id, const float lo
 // climb ends well within this cap; it only guards against corrupted input.
 constexpr int kMaxDepth = 256;
 
+// all lanes of the wave have issued their LDS accesses before any lane's
+// later ones (LDS executes a wave's accesses in order; this keeps the
+// compiler from moving them across)
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace
 }  // namespace lbvh

@@ -4,7 +4,7 @@
 #pragma once
 #pragma clang fp contract(off)
 
-#include "lbvh_internal.hpp"
+#include "device_common.hpp"
 
 namespace lbvh {
 namespace {
@@ -270,16 +270,6 @@ struct Tree {
 };
 
 constexpr int kWavesPerBlock = kBlock / 64;
-
-// all lanes of the wave have issued their LDS accesses before any lane's
-// later ones (LDS executes a wave's accesses in order; this keeps the
-// compiler from moving them across)
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // set lanes of mask below this lane
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
