@@ -6,6 +6,7 @@
 //   k_morton                   Morton code per primitive + the digit
 //                              histograms of every radix pass
 //   k_onesweep (x passes)      LSD radix pass with decoupled look-back
+//   k_scene_sort               all of the above in one block, for small trees
 //   k_bottomup_l0 / _up        Alg. 4 in levels of blocks: leaves up, one
 //                              CAS per internal node, Karras-ordered parents
 //                              with left child, rope and box written by the
@@ -20,6 +21,7 @@
 #include "bottomup.hpp"
 #include "device_common.hpp"
 #include "radix_sort.hpp"
+#include "scene_sort.hpp"
 
 namespace lbvh {
 namespace {
@@ -174,7 +176,12 @@ constexpr size_t sort_lds_bytes(int key_bytes, int threads, int items, int bits)
 //   63-bit,  9 bits: 512 x 8    2^10  67 / 100,  2^14 109 / 148,  2^18 181 / 214
 //                    1024 x 8   2^20 279 / 296
 //            8 bits: 1024 x 16  2^22 532 / 604,  2^23 918 / 955
-struct SortPlan { int bits, variant; };
+// Up to 4096 primitives, a tile of one block, that block does everything up
+// to the sorted codes (one launch for 6 to 10, whose starts were most of the
+// time): 2^10 30-bit 40 -> 23, 63-bit 66 -> 30; 4096 60 -> 46, 94 -> 61.  From
+// two tiles on it loses: 8000 30-bit 67 -> 83, 63-bit 105 -> 114.
+struct SortPlan { bool one_block; int bits, variant; };
+constexpr int kOneBlockMax = 4096;
 
 template <typename K>
 SortPlan sort_plan(int64_t n)
@@ -184,7 +191,8 @@ SortPlan sort_plan(int64_t n)
     constexpr int shape_knob = short_codes ? TUNE_SORT_VARIANT32 : TUNE_SORT_VARIANT64;
     if (tune_is_default(bits_knob) && tune_is_default(shape_knob)) {
         const int variant = n <= (short_codes ? 1 << 17 : 1 << 19) ? 3 : (n <= (1 << 21) ? 5 : 7);
-        return {short_codes ? 10 : (variant == 7 ? 8 : 9), variant};
+        const bool one = n <= kOneBlockMax && tune_get(TUNE_RADIX_MODE) == 0;
+        return {one, short_codes ? 10 : (variant == 7 ? 8 : 9), variant};
     }
     const int bits = radix_bits(short_codes ? 30 : 63);
     const int64_t v = tune_get(shape_knob);
@@ -192,7 +200,7 @@ SortPlan sort_plan(int64_t n)
     const SortShape sh = kSortShapes[var];
     const bool fits = sh.threads * sh.items >= radix_min_tile(bits) &&
                       sort_lds_bytes(sizeof(K), sh.threads, sh.items, bits) <= 150 * 1024;
-    return {bits, fits ? var : (short_codes ? 4 : 3)};   // 512 x 16 / 512 x 8 fit every width
+    return {false, bits, fits ? var : (short_codes ? 4 : 3)};   // 512 x 16 / 512 x 8 fit every width
 }
 
 // One radix pass: the onesweep kernel alone, or (toff given: the
@@ -310,34 +318,49 @@ hipError_t run_build(const float *prims, int n, int code_bits, lbvh_node *nodes_
     const SortPlan plan = sort_plan<K>(n);
     const int bits = plan.bits;
 
-    const int64_t groups = (int64_t)n / P::G;
-    int nb = (int)((groups + 4 * kBlock - 1) / (4 * kBlock));
-    nb = nb < 1 ? 1 : (nb > kBoundsBlocksMax ? kBoundsBlocksMax : nb);
-    prof_begin(K_BOUNDS, s);
-    hipLaunchKernelGGL((k_bounds<KIND>), dim3(nb), dim3(kBlock), 0, s, prims, n, partials);
-    prof_end(K_BOUNDS, s);
-    prof_begin(K_BOUNDS_FINAL, s);
-    hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, s, partials, nb, code_bits / 3,
-                       scene, ctrl, hist, (int)((int64_t)radix_passes(code_bits, bits) << bits));
-    prof_end(K_BOUNDS_FINAL, s);
-
-    if constexpr (sizeof(K) == 4) {
-        if (bits == 10)
-            run_sort<KIND, K, 10>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                  keys_alt, vals, plan.variant, s);
+    if (plan.one_block) {
+        constexpr int B = sizeof(K) == 4 ? 10 : 9;
+        K *ka = (radix_passes(code_bits, B) & 1) ? keys_alt : codes;
+        K *kb = ka == codes ? keys_alt : codes;
+        prof_begin(K_SORT, s);
+#define LBVH_ONE_ARGS prims, (const int64_t *)nullptr, (const int32_t *)nullptr, (uint32_t)n, code_bits, scene, \
+                      ka, kb, vals[0], vals[1], leaf_perm, ctrl + kCtrlError
+        if (n <= 1024)
+            hipLaunchKernelGGL((k_scene_sort<KIND, K, B, 1024, 1>), dim3(1), dim3(1024), 0, s, LBVH_ONE_ARGS);
         else
-            run_sort<KIND, K, 8>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                 keys_alt, vals, plan.variant, s);
+            hipLaunchKernelGGL((k_scene_sort<KIND, K, B, 1024, 4>), dim3(1), dim3(1024), 0, s, LBVH_ONE_ARGS);
+#undef LBVH_ONE_ARGS
+        prof_end(K_SORT, s);
     } else {
-        if (bits == 11)
-            run_sort<KIND, K, 11>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                  keys_alt, vals, plan.variant, s);
-        else if (bits == 9)
-            run_sort<KIND, K, 9>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                 keys_alt, vals, plan.variant, s);
-        else
-            run_sort<KIND, K, 8>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
-                                 keys_alt, vals, plan.variant, s);
+        const int64_t groups = (int64_t)n / P::G;
+        int nb = (int)((groups + 4 * kBlock - 1) / (4 * kBlock));
+        nb = nb < 1 ? 1 : (nb > kBoundsBlocksMax ? kBoundsBlocksMax : nb);
+        prof_begin(K_BOUNDS, s);
+        hipLaunchKernelGGL((k_bounds<KIND>), dim3(nb), dim3(kBlock), 0, s, prims, n, partials);
+        prof_end(K_BOUNDS, s);
+        prof_begin(K_BOUNDS_FINAL, s);
+        hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, s, partials, nb, code_bits / 3,
+                           scene, ctrl, hist, (int)((int64_t)radix_passes(code_bits, bits) << bits));
+        prof_end(K_BOUNDS_FINAL, s);
+
+        if constexpr (sizeof(K) == 4) {
+            if (bits == 10)
+                run_sort<KIND, K, 10>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
+                                      keys_alt, vals, plan.variant, s);
+            else
+                run_sort<KIND, K, 8>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
+                                     keys_alt, vals, plan.variant, s);
+        } else {
+            if (bits == 11)
+                run_sort<KIND, K, 11>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
+                                      keys_alt, vals, plan.variant, s);
+            else if (bits == 9)
+                run_sort<KIND, K, 9>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
+                                     keys_alt, vals, plan.variant, s);
+            else
+                run_sort<KIND, K, 8>(prims, n, code_bits, codes, leaf_perm, scene, ctrl, hist, status,
+                                     keys_alt, vals, plan.variant, s);
+        }
     }
 
     prof_begin(K_BOTTOMUP, s);

@@ -25,6 +25,21 @@ def test_single_build_lines(n, bits):
 
 
 @pytest.mark.parametrize("bits", [30, 63])
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("n", [1, 2, 63, 65, 1023, 1024, 1025, 4095, 4096, 4097])
+def test_one_block_build(n, kind, bits):
+    import paper_2402_00665_amd as lb
+    rng = np.random.default_rng([n, bits, kind])
+    prims = np.round(rng.random((n, 3)) * 64).astype(np.float32)   # many equal codes
+    if kind == 1:
+        prims = np.concatenate([prims, prims + rng.random((n, 3), dtype=np.float32)], axis=1)
+    ws = lb.Workspace()
+    for _ in range(2):                        # the second into a used workspace
+        tree, _ = gpu_build(prims, kind, bits, ws)
+        assert_tree_equal(tree, oracle.build(kind, prims, bits))
+
+
+@pytest.mark.parametrize("bits", [30, 63])
 @pytest.mark.parametrize("sizes", [
     [4096, 4095, 1], [4097, 4096, 0],                    # a scene of one tile, and beyond
     [5000] * 128, [5000] * 127 + [4999],                 # 128 times the largest, and below
