@@ -302,13 +302,14 @@ constexpr BatchSortShape kBatchShapes[] = {{256, 16}, {256, 8}, {512, 8}, {512, 
 // How a batch of N primitives in scenes of at most max_scene is sorted: one
 // block per scene or segmented passes, digit width, shape.  The knobs' choice,
 // unless mode, shape and width stand at their defaults.  Then one block per
-// scene where it sorts a scene on chip (up to a tile of 4096), or where there
-// are so many scenes that the largest block, alone with max_scene keys, is not
+// scene where it sorts a scene on chip (up to a tile of 4096 or 8192), or where
+// there are so many scenes that the largest block, alone with max_scene keys, is not
 // what takes the time (us of whole 63-bit builds, block against segmented:
-// 64 scenes up to 4000: 70 / 105, 4096 up to 65536 (537 times the largest):
+// 64 scenes up to 4000: 70 / 105, with their queries 83 up to 5569: 175 / 208,
+// 4096 up to 65536 (537 times the largest):
 // 2551 / 3942, 300 up to 250000 (157 times): 3854 / 4168, but 512 up to 65536
 // (55 times): 727 / 568).  Blocks of 512 x 8, or 1024 x 8 where scenes exceed
-// 65536; segmented passes of 512 x 8 and 10 or 9 bits (568 against 596 us on
+// 65536, or 4096 and are few; segmented passes of 512 x 8 and 10 or 9 bits (568 against 596 us on
 // those 512 scenes with 256 x 16).
 struct BatchPlan { bool block; int bits, variant; };
 
@@ -321,8 +322,9 @@ BatchPlan batch_plan(int64_t N, int64_t max_scene, int levels, int code_bits)
     const bool can = levels <= 1;
     if (tune_is_default(TUNE_BATCH_SORT_MODE) && tune_is_default(TUNE_BATCH_SORT) &&
         tune_is_default(short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64)) {
-        if (can && (max_scene <= 4096 || N >= 128 * max_scene))
-            return {true, short_codes ? 8 : 9, max_scene > 65536 ? 2 : 1};
+        const bool many = N >= 128 * max_scene;
+        if (can && (max_scene <= 8192 || many))
+            return {true, short_codes ? 8 : 9, max_scene > (many ? 65536 : 4096) ? 2 : 1};
         return {false, short_codes ? 10 : 9, 2};
     }
     const int bits = radix_bits(code_bits);

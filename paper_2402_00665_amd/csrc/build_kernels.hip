@@ -176,6 +176,10 @@ constexpr size_t sort_lds_bytes(int key_bytes, int threads, int items, int bits)
 //   63-bit,  9 bits: 512 x 8    2^10  67 / 100,  2^14 109 / 148,  2^18 181 / 214
 //                    1024 x 8   2^20 279 / 296
 //            8 bits: 1024 x 16  2^22 532 / 604,  2^23 918 / 955
+// A CU holds one such block at 63 bits, so passes run in rounds of 256 tiles:
+// where 9 bits in 768 x 16 takes no more rounds than 1024 x 16, its seven
+// passes beat eight (2.6 M 393 against 416, 5.5 M 662 / 689; but 3.2 M, a
+// second round, 508 / 455, and 7 M 815 / 789).
 // Up to 4096 primitives, a tile of one block, that block does everything up
 // to the sorted codes (one launch for 6 to 10, whose starts were most of the
 // time): 2^10 30-bit 40 -> 23, 63-bit 66 -> 30; 4096 60 -> 46, 94 -> 61.  From
@@ -190,7 +194,9 @@ SortPlan sort_plan(int64_t n)
     constexpr int bits_knob = short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64;
     constexpr int shape_knob = short_codes ? TUNE_SORT_VARIANT32 : TUNE_SORT_VARIANT64;
     if (tune_is_default(bits_knob) && tune_is_default(shape_knob)) {
-        const int variant = n <= (short_codes ? 1 << 17 : 1 << 19) ? 3 : (n <= (1 << 21) ? 5 : 7);
+        const int64_t round6 = 256 * 768 * 16, round7 = 256 * 1024 * 16;
+        const int large = !short_codes && (n + round6 - 1) / round6 == (n + round7 - 1) / round7 ? 6 : 7;
+        const int variant = n <= (short_codes ? 1 << 17 : 1 << 19) ? 3 : (n <= (1 << 21) ? 5 : large);
         const bool one = n <= kOneBlockMax && tune_get(TUNE_RADIX_MODE) == 0;
         return {one, short_codes ? 10 : (variant == 7 ? 8 : 9), variant};
     }

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bits", [30, 63])
-@pytest.mark.parametrize("n", [1 << 17, (1 << 17) + 1, 1 << 19, (1 << 19) + 1, 1 << 21, (1 << 21) + 1])
+@pytest.mark.parametrize("n", [1 << 17, (1 << 17) + 1, 1 << 19, (1 << 19) + 1, 1 << 21, (1 << 21) + 1,
+                               3 << 20, (3 << 20) + 1, (1 << 22) + 1])
 def test_single_build_lines(n, bits):
     rng = np.random.default_rng([n, bits])
     prims = rng.random((n, 3), dtype=np.float32)
@@ -42,6 +43,7 @@ def test_one_block_build(n, kind, bits):
 @pytest.mark.parametrize("bits", [30, 63])
 @pytest.mark.parametrize("sizes", [
     [4096, 4095, 1], [4097, 4096, 0],                    # a scene of one tile, and beyond
+    [8192, 8191, 3], [8193, 8192],
     [5000] * 128, [5000] * 127 + [4999],                 # 128 times the largest, and below
     [65536, 70000], [65537] * 128,                       # the larger blocks' side
 ])
