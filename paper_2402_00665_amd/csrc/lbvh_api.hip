@@ -63,7 +63,7 @@ QueryLayout query_layout(int64_t m)
     L.places = take(tasks * L.packet * sizeof(int32_t));
     L.scan_status = take((mm / kScanTile + 1) * sizeof(uint64_t));
     L.deep = 0;
-    const size_t share = (size_t)ray_share(m), deep_lanes = (mm + share - 1) / share * kRayBlock;
+    const size_t share = (size_t)ray_share(m), deep_lanes = (mm + share - 1) / share * ray_lanes((int)share);
     off = std::max(off, align256(deep_lanes * (kRayDepth - kRayStack) * 8));
     L.ctrl = take(128);
     L.total = off;

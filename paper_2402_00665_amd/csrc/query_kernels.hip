@@ -117,20 +117,25 @@ __global__ __launch_bounds__(kBlock) void k_query_reset(QueryCtrl *ctrl, int ord
 // instructions, so what counts is waves per CU: the first kRayStack stack
 // entries lie in LDS and the rest, rarely reached, in the call's workspace
 // (2^20 rays on 2^24 clustered boxes: 0.96 ms with 6 entries in LDS, 1.04
-// with 8, 1.00 with 10).  A wave owns `share` rays; a lane whose ray is done takes the
-// next one, kRayRefill lanes at a time (1.02 ms without).  One walk in
-// preorder along the ropes per ray took 11.3 ms: it visits the children in
-// index order, so most of what it visits lies behind the hit.
-constexpr int kRayRefill = 8;
+// with 8, 1.00 with 10).  A wave owns `share` rays; once kRayRefill lanes
+// have ended their rays, those lanes write their results and take the next
+// rays together (1.02 ms for 2^20 rays without refills; writing each result
+// as its ray ends, 1.00 instead of 0.92).  An entry on the stack carries its
+// split, or its first step would load it (10^5 rays on 10^6 boxes 191 -> 163
+// us).  Few rays are spread, down to one a wave: a wave takes the steps of
+// its slowest ray and both sides of every branch (97 rays on 423177 boxes
+// 136 -> 59 us).  One walk in preorder along the ropes per ray took 11.3 ms:
+// it visits the children in index order, so most of what it visits lies
+// behind the hit.
+constexpr int kRayRefill = 16;
 
 struct FirstHit {
     float best;
-    int pos;   // leaf position of the best hit (-1: none)
-    __device__ bool better(float e, int l) const
-    {
-        return pos < 0 || e < best || (e == best && l < pos);
-    }
+    int pos;   // leaf position of the best hit (kNoHit: none)
+    // e of a box that was met is not NaN; no short circuit, so no branches
+    __device__ bool better(float e, int l) const { return (e < best) | ((e == best) & (l < pos)); }
 };
+constexpr int kNoHit = 0x7fffffff;
 
 __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *__restrict__ rays, int m,
                                                          int share, int32_t *__restrict__ hit,
@@ -138,9 +143,11 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
 {
     __shared__ int2 s_stack[kRayStack][kRayBlock];    // node, other end of its range
     __shared__ float s_enter[kRayStack][kRayBlock];   // its entry parameter
+    __shared__ int s_split[kRayStack][kRayBlock];     // its split
     const int leaf0 = tr.leaf0(), tid = threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * kRayBlock;
-    deep += (int64_t)blockIdx.x * kRayBlock + tid;
+    const int lanes = share < kRayBlock ? share : kRayBlock;   // that ever hold a ray
+    const int64_t stride = (int64_t)gridDim.x * lanes;
+    deep += (int64_t)blockIdx.x * lanes + tid;
     auto split_of = [&](int c) { return c >= leaf0 ? c - leaf0 : c; };
     float4 root_a, root_b;
     tr.load(0, root_a, root_b);
@@ -152,18 +159,36 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
     int64_t budget = 0;
     FastRay q{};
     bool fast = true;
-    FirstHit f{INFINITY, -1};
+    FirstHit f{INFINITY, kNoHit};
+    bool live = false;
     while (true) {
-        const uint64_t idle = __ballot(j < 0);
-        if (idle != 0 && next < end && (__popcll(idle) >= kRayRefill || idle == ~0ull)) {
+        const uint64_t idle = __ballot(!live);
+        if (idle == ~0ull || (next < end && __popcll(idle) >= kRayRefill)) {
+            // the rays that ended since: their results
+            if (!live && j >= 0) {
+                int prim = -1;
+                float best = INFINITY;
+                if (f.pos != kNoHit) {   // the entry parameter exactly as the test defines it
+                    Ray x;
+                    x.load(rays, j);
+                    float4 a, b;
+                    tr.load(leaf0 + f.pos, a, b);
+                    x.enter(a, b, &best);
+                    prim = __float_as_int(a.w);
+                }
+                hit[j] = prim;
+                t[j] = best;
+                j = -1;
+            }
+            if (next >= end) break;   // every lane is idle
             const int64_t mine = next + lanes_below(idle);
             next += __popcll(idle);
-            if (j < 0 && mine < end) {
+            if (!live && mine < end) {
                 Ray x;
                 x.load(rays, (int)mine);
                 q = FastRay(x);
                 fast = x.plain();
-                f = FirstHit{INFINITY, -1};
+                f = FirstHit{INFINITY, kNoHit};
                 budget = tr.walk_budget();
                 sp = 0;
                 l = 0;
@@ -173,6 +198,7 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
                 const bool met = x.enter(root_a, root_b, &e);
                 if (met && leaf0 > 0) {
                     j = (int)mine;
+                    live = true;
                 } else {
                     hit[mine] = met ? __float_as_int(root_a.w) : -1;
                     t[mine] = met ? e : INFINITY;
@@ -180,8 +206,7 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
             }
             continue;
         }
-        if (idle == ~0ull) break;
-        if (j >= 0) {
+        if (live) {
             const bool lleaf = g == l, rleaf = g + 1 == r;
             float4 la, lb, ra, rb;
             tr.load(lleaf ? leaf0 + g : g, la, lb);
@@ -197,12 +222,16 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
                 hl = x.enter(la, lb, &el);
                 hr = x.enter(ra, rb, &er);
             }
-            hl = hl && f.better(el, l);
-            if (hl && lleaf) f = FirstHit{el, l};
-            hr = hr && f.better(er, g + 1);
-            if (hr && rleaf) f = FirstHit{er, r};
-            hl = hl && !lleaf && f.better(el, l);
-            hr = hr && !rleaf;
+            auto take = [&](bool now, float e, int leaf) {
+                f.best = now ? e : f.best;
+                f.pos = now ? leaf : f.pos;
+            };
+            hl = hl & f.better(el, l);
+            take(hl & lleaf, el, l);
+            hr = hr & f.better(er, g + 1);
+            take(hr & rleaf, er, r);
+            hl = hl & !lleaf & f.better(el, l);
+            hr = hr & !rleaf;
             const int gl = split_of(__float_as_int(la.w)), gr = split_of(__float_as_int(ra.w));
             const bool lnear = hl && (!hr || el <= er);
             if (hl && hr) {
@@ -211,6 +240,7 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
                 if (sp < kRayStack) {
                     s_stack[sp][tid] = far;
                     s_enter[sp][tid] = fe;
+                    s_split[sp][tid] = lnear ? gr : gl;
                 } else {
                     deep[(sp - kRayStack) * stride] = far;
                 }
@@ -228,41 +258,26 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
                     if (sp < kRayStack) {
                         s = s_stack[sp][tid];
                         e = s_enter[sp][tid];
-                    } else {   // its entry parameter is computed again
+                        g = s_split[sp][tid];
+                    } else {   // its entry parameter and split are found again
                         s = deep[(sp - kRayStack) * stride];
                         Ray x;
                         x.load(rays, j);
                         float4 a, b;
                         tr.load(s.x, a, b);
                         x.enter(a, b, &e);
+                        g = split_of(__float_as_int(a.w));
                     }
                     l = s.x < s.y ? s.x : s.y;
                     go = f.better(e, l);
                 }
-                if (go) {
-                    r = s.x < s.y ? s.y : s.x;
-                    g = split_of(__float_as_int(tr.nodes[2 * (int64_t)s.x].w));
-                }
+                r = s.x < s.y ? s.y : s.x;
             }
             if (--budget < 0 && go) {
                 tr.budget_spent();
                 go = false;
             }
-            if (!go) {
-                int prim = -1;
-                float best = INFINITY;
-                if (f.pos >= 0) {   // the entry parameter exactly as the test defines it
-                    Ray x;
-                    x.load(rays, j);
-                    float4 a, b;
-                    tr.load(leaf0 + f.pos, a, b);
-                    x.enter(a, b, &best);
-                    prim = __float_as_int(a.w);
-                }
-                hit[j] = prim;
-                t[j] = best;
-                j = -1;
-            }
+            live = go;
         }
     }
 }

@@ -230,3 +230,20 @@ def test_first_hit_nearer_child_first(n, m, ws):
         rhit, rt, _ = oracle.ray_first_traverse(rays, ref)
         hit, t = gpu_first(tree, rays, ws)
         assert_first_equal(hit, t, rhit, rt)
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 5), (300, 4096), (300, 4097), (5000, 8193), (700, 258048), (700, 262145),
+                                 (700, 393217)])
+def test_first_hit_rays_per_wave(n, m, ws):
+    """Both sides of each count of rays where a wave's share of them grows
+    (one, two, three, 63 and 64 a wave), with rays that miss everything."""
+    rng = np.random.default_rng([53, n, m])
+    c = rng.random((n, 3))
+    boxes = np.concatenate([c - 0.05, c + 0.05 * rng.random((n, 3))], 1).astype(np.float32)
+    rays = workloads.rays_toward(rng.random((m, 3), dtype=np.float32), rng)
+    rays[::3, :3] += np.float32(9.0)
+    ref = oracle.build(1, boxes, 30)
+    tree, _ = gpu_build(boxes, 1, 30, ws)
+    rhit, rt, _ = oracle.ray_first_traverse(rays, ref)
+    hit, t = gpu_first(tree, rays, ws)
+    assert_first_equal(hit, t, rhit, rt)
