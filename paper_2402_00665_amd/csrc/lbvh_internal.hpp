@@ -44,7 +44,7 @@ constexpr int kCutGrid = 1024;          // most blocks of the kernel over heavy 
 constexpr int kOwnTasks = 8;            // places for tasks that every packet has of its own
 constexpr int kTaskGrid = 16384;        // ... of the kernels over their tasks
 constexpr int kQOrderMin = 32768;     // queries from which they are sorted and share packets
-constexpr int kQOrderTile = 2048;     // keys per tile of the query-order sort (512 x 4)
+constexpr int kQOrderTile = 2048;     // smallest tile of the query-order sort
 constexpr int kQOrderPasses = 2;      // 16-bit query-order keys: two 8-bit digits
 constexpr int kQOrderKeyBlocks = 256;  // blocks of the query-order key kernel
 constexpr int kHitCache = 32;        // light-walk hits of a query kept for the fill

@@ -404,14 +404,17 @@ __global__ void k_zero_i64(int64_t *p, int64_t count, uint32_t *err)
 // total), and into a second copy where `copy` is not null.  One launch: a
 // block takes the next tile of kScanTile counts from a counter (so every
 // tile it waits for is already running), publishes the tile's sum and adds
-// up the earlier tiles' with a decoupled look-back, one wave reading 64
-// status words at a time.  A status word holds two flag bits over a 62-bit
+// up the earlier tiles' with a decoupled look-back, one wave reading 4 x 64
+// status words at a time (bound by the latency of these reads, which cross
+// the chip; with 64 at a time and offsets stored 64 bytes apart per lane,
+// 2^20 counts took 24 instead of 16 us).  A status word holds two flag bits over a 62-bit
 // sum, so it needs no fence.  Words and counter are zero on entry.  A wait
 // that never ends (not expected) is cut and flagged.  Three launches
 // (sums, their scan, the final pass) took 58 us over 2^20 counts and three
 // scans, and about 10 us when there was nothing to scan.
 constexpr uint64_t kScanSum = 1ull << 62, kScanPrefix = 2ull << 62, kScanValue = (1ull << 62) - 1;
 constexpr uint32_t kQErrScan = 6;
+constexpr int kScanAhead = 4;   // look-back words per lane in flight
 
 inline int64_t scan_tiles(int64_t m) { return (m + kScanTile - 1) / kScanTile; }
 
@@ -423,6 +426,7 @@ __global__ __launch_bounds__(kBlock) void k_scan(const int32_t *__restrict__ cou
     __shared__ int64_t sh[kBlock / 64];
     __shared__ uint32_t s_tile;
     __shared__ int64_t s_before;
+    __shared__ int64_t s_run[kBlock * (kScanItems + 1)];   // rows apart in the banks
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (threadIdx.x == 0) s_tile = gridDim.x > 1 ? atomicAdd(counter, 1u) : 0u;
     __syncthreads();
@@ -430,11 +434,18 @@ __global__ __launch_bounds__(kBlock) void k_scan(const int32_t *__restrict__ cou
     const int64_t base = tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int32_t c[kScanItems];
     int64_t sum = 0;
+    if (base + kScanItems <= m) {   // counts is aligned to 16 bytes
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        c[k] = base + k < m ? counts[base + k] : 0;
-        sum += c[k];
+        for (int k = 0; k < kScanItems; k += 4) {
+            const int4 v = *reinterpret_cast<const int4 *>(counts + base + k);
+            c[k] = v.x; c[k + 1] = v.y; c[k + 2] = v.z; c[k + 3] = v.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) c[k] = base + k < m ? counts[base + k] : 0;
     }
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) sum += c[k];
     int64_t x = sum;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -455,27 +466,36 @@ __global__ __launch_bounds__(kBlock) void k_scan(const int32_t *__restrict__ cou
         if (wave == 0) {
             int64_t found = 0;
             uint32_t spins = 0;
-            for (int64_t j = tile - 1; j >= 0;) {   // lane l reads tile j - l
-                const uint64_t s = j >= lane ? __hip_atomic_load(status + j - lane, __ATOMIC_RELAXED,
-                                                                 __HIP_MEMORY_SCOPE_AGENT)
-                                             : kScanPrefix;
-                const uint64_t empty = __ballot((s >> 62) == 0), prefix = __ballot((s >> 62) == 2);
-                const int upto = prefix ? __ffsll((unsigned long long)prefix) - 1 : 63;   // last lane to add
-                if (empty & (upto == 63 ? ~0ull : (2ull << upto) - 1ull)) {
-                    if (++spins > (1u << 22)) {   // never expected: bounded wait
-                        if (lane == 0)
-                            __hip_atomic_store(err, kQErrScan, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            bool done = tile == 0;
+            for (int64_t j = tile - 1; !done;) {   // word u of lane l: tile j - 64 u - l
+                uint64_t s[kScanAhead];
+#pragma unroll
+                for (int u = 0; u < kScanAhead; ++u)
+                    s[u] = j - 64 * u >= lane ? __hip_atomic_load(status + j - 64 * u - lane, __ATOMIC_RELAXED,
+                                                                  __HIP_MEMORY_SCOPE_AGENT)
+                                              : kScanPrefix;
+#pragma unroll
+                for (int u = 0; u < kScanAhead; ++u) {
+                    const uint64_t empty = __ballot((s[u] >> 62) == 0), prefix = __ballot((s[u] >> 62) == 2);
+                    const int upto = prefix ? __ffsll((unsigned long long)prefix) - 1 : 63;   // last lane to add
+                    if (empty & (upto == 63 ? ~0ull : (2ull << upto) - 1ull)) {
+                        if (++spins > (1u << 22)) {   // never expected: bounded wait
+                            if (lane == 0)
+                                __hip_atomic_store(err, kQErrScan, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            done = true;
+                        }
+                        __builtin_amdgcn_s_sleep(1);
                         break;
                     }
-                    __builtin_amdgcn_s_sleep(1);
-                    continue;
-                }
-                int64_t v = lane <= upto ? (int64_t)(s & kScanValue) : 0;
+                    int64_t v = lane <= upto ? (int64_t)(s[u] & kScanValue) : 0;
 #pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-                found += v;
-                if (prefix) break;
-                j -= 64;
+                    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+                    found += v;
+                    done = prefix != 0;
+                    if (done) break;
+                    j -= 64;
+                    // the words after this one were read relative to the old j
+                }
             }
             if (lane == 0) {
                 s_before = found;
@@ -489,14 +509,23 @@ __global__ __launch_bounds__(kBlock) void k_scan(const int32_t *__restrict__ cou
     int64_t run = before + x - sum;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < m) {
-            offsets[base + k] = run;
-            if (copy) copy[base + k] = run;
-        }
+        s_run[threadIdx.x * (kScanItems + 1) + k] = run;
         run += c[k];
         if (base + k == m - 1) {
             offsets[m] = run;
             if (copy) copy[m] = run;
+        }
+    }
+    __syncthreads();
+    // a wave's offsets leave as one run
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        const int i = k * kBlock + threadIdx.x;
+        const int64_t j = tile * kScanTile + i;
+        if (j < m) {
+            const int64_t v = s_run[i / kScanItems * (kScanItems + 1) + i % kScanItems];
+            offsets[j] = v;
+            if (copy) copy[j] = v;
         }
     }
 }

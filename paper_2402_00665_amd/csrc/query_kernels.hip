@@ -334,6 +334,28 @@ unsigned grid_for(int64_t items, int64_t most)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + kBlock - 1) / kBlock, most));
 }
 
+// Queries in key order: keys, then two stable 8-bit passes.  From 2^18
+// queries on in tiles of 1024 x 8, whose passes look back over a quarter of
+// the tiles (a pass over 2^20 keys 26.2 -> 18.5 us); below, 512 x 4 makes
+// enough blocks.
+constexpr int64_t kQOrderLarge = 1 << 18;
+constexpr int kSmallTree = 1 << 18;
+
+template <class Q, int T, int I>
+void sort_keys(const Tree &tr, const float *q, int m, unsigned key_blocks, const Scratch &S, hipStream_t s)
+{
+    const unsigned tiles = (unsigned)(((int64_t)m + T * I - 1) / (T * I));
+    hipLaunchKernelGGL((k_qorder_keys<Q>), dim3(key_blocks), dim3(kBlock), 0, s, tr, q, m, S.qkeys[0], S.qhist,
+                       S.qstatus[0], (int64_t)tiles * kRadix);
+    const SortSegs one{nullptr, nullptr, 1, 0};
+    hipLaunchKernelGGL((k_onesweep<uint32_t, T, I, kRadixBits>), dim3(tiles), dim3(T), 0, s, S.qkeys[0],
+                       S.qkeys[1], nullptr, S.qvals, (int64_t)m, one, 0, kRadixBits, S.qhist, S.qstatus[0],
+                       S.qstatus[1], tiles, S.ctrl->sort_tile, tr.err, (const uint32_t *)nullptr);
+    hipLaunchKernelGGL((k_onesweep<uint32_t, T, I, kRadixBits>), dim3(tiles), dim3(T), 0, s, S.qkeys[1],
+                       S.qkeys[0], S.qvals, S.perm, (int64_t)m, one, kRadixBits, kRadixBits, S.qhist + kRadix,
+                       S.qstatus[1], nullptr, 0u, S.ctrl->sort_tile + 1, tr.err, (const uint32_t *)nullptr);
+}
+
 template <class Q>
 hipError_t run_count(Tree tr, const float *q, int m, int64_t *offsets, char *ws,
                      const QueryLayout &L, hipStream_t s)
@@ -349,20 +371,12 @@ hipError_t run_count(Tree tr, const float *q, int m, int64_t *offsets, char *ws,
     if (order) {
         // sort the queries' numbers by key (two stable 8-bit passes)
         prof_begin(K_QORDER, s);
-        const int64_t qtiles = ((int64_t)m + kQOrderTile - 1) / kQOrderTile;
         // few blocks, so that few global histogram adds meet on each word
         const unsigned gk = (unsigned)std::min<int64_t>(kQOrderKeyBlocks, (m + 16 * kBlock - 1) / (16 * kBlock));
-        hipLaunchKernelGGL((k_qorder_keys<Q>), dim3(gk), dim3(kBlock), 0, s, tr, q, m, S.qkeys[0],
-                           S.qhist, S.qstatus[0], qtiles * kRadix);
-        const SortSegs one{nullptr, nullptr, 1, 0};
-        hipLaunchKernelGGL((k_onesweep<uint32_t, 512, 4, kRadixBits>), dim3((unsigned)qtiles), dim3(512), 0, s,
-                           S.qkeys[0], S.qkeys[1], nullptr, S.qvals, (int64_t)m, one, 0, kRadixBits, S.qhist,
-                           S.qstatus[0], S.qstatus[1], (uint32_t)qtiles, S.ctrl->sort_tile, tr.err,
-                           (const uint32_t *)nullptr);
-        hipLaunchKernelGGL((k_onesweep<uint32_t, 512, 4, kRadixBits>), dim3((unsigned)qtiles), dim3(512), 0, s,
-                           S.qkeys[1], S.qkeys[0], S.qvals, S.perm, (int64_t)m, one, kRadixBits, kRadixBits,
-                           S.qhist + kRadix, S.qstatus[1], nullptr, 0u, S.ctrl->sort_tile + 1, tr.err,
-                           (const uint32_t *)nullptr);
+        if (m < kQOrderLarge)
+            sort_keys<Q, 512, kQOrderTile / 512>(tr, q, m, gk, S, s);
+        else
+            sort_keys<Q, 1024, 8>(tr, q, m, gk, S, s);
         prof_end(K_QORDER, s);
     }
     prof_begin(K_QCOUNT, s);
@@ -373,7 +387,11 @@ hipError_t run_count(Tree tr, const float *q, int m, int64_t *offsets, char *ws,
     // 64 leaves 200 heavy spheres at 148 instead of 117 us), and leaves of a
     // task: wide enough that a packet of 64 makes few thousand of them, narrow
     // for packets of few queries, whose tasks are cheap
-    const int patience = 3 << std::min<int64_t>(std::max<int64_t>(0, tune_get(TUNE_QSPLIT2) - 3), 16);
+    // (twice as many where the queries fill the machine on a tree of less than
+    // 2^18 primitives, whose long walks end soon by themselves: 909012 spheres
+    // on 141193 boxes 258 -> 231 us, but boxes on 400000 228 -> 299)
+    const int patience = (L.packets > kDrainWaves && tr.n < kSmallTree ? 6 : 3)
+                         << std::min<int64_t>(std::max<int64_t>(0, tune_get(TUNE_QSPLIT2) - 3), 16);
     const int wider = tune_get(TUNE_QLEAF) == 1 ? 4 : 1;
     const int width = wider * (int)std::max<int64_t>(512, (int64_t)size << std::max<int64_t>(0, tune_get(TUNE_QSPLIT1) - 7));
     hipLaunchKernelGGL((k_walk<Q>), dim3((unsigned)L.packets), dim3(kWalkBlock), 0, s, tr, q, m, size, patience,

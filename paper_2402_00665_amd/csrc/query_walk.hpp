@@ -53,6 +53,7 @@ struct QueryCtrl {   // the count call's control words, zeroed at its start
     uint32_t own;        // some packet's tasks lie in places of its own
     uint32_t error;      // at kQueryErrorByte
     uint32_t sort_tile[2];
+    uint32_t steps;      // of the waves that `done` counts, in units of kStepUnit
 };
 static_assert(offsetof(QueryCtrl, error) == kQueryErrorByte, "error word");
 
@@ -89,6 +90,12 @@ constexpr int kLookEvery = 32;   // steps between looks at the other waves
 // one wave in so many counts itself done: adds to one word take turns, about
 // 8 ns each (10^4 waves that all did: 77 us on a walk of 56)
 constexpr uint32_t kSample = 16;
+constexpr int kStepUnit = 4;        // the sum of steps counts in these
+// ... and while it runs dry a packet is only worth cutting when it has taken
+// this many times the mean walk's steps, or kLongCall (2^20 spheres of 8 hits
+// 939 us without, 892 at 2, 878 at 3, 897 at 4; 2^20 segments, whose mean is
+// long, 16.0 ms without, 17.9 at 3 with no kLongCall)
+constexpr int kLongFor = 3, kLongCall = 512;
 constexpr int kLongWalk = 1 << 16;  // steps after which a packet leaves its rest in any case
 constexpr int kLongRange = 4096;    // leaves of a contained range that a light walk leaves to others
 constexpr int kDrainWaves = 1024;   // walking waves at which the machine runs dry: one a SIMD (512 and 2048: slower)
@@ -117,8 +124,8 @@ struct PacketRun {
     int l, r, g;              // the node it starts at: leaf range, split (l -1: the root)
     uint64_t in, all;         // its queries there
     int from;                 // this lane's query: first leaf that counts
-    const uint32_t *done;     // light walks: waves finished so far, and in all (else null)
-    uint32_t waves;
+    const QueryCtrl *ctrl;    // light walks: counts the waves that finished (else null),
+    uint32_t waves;           // ... of so many
     int patience;             // steps before it may leave the rest to others
 };
 
@@ -132,7 +139,7 @@ struct PacketRun {
 template <class Q, class T, bool FILL>
 __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run, const Q &q, bool mine,
                                            PacketLds<Q> &lds, int32_t *__restrict__ out, int64_t out_at,
-                                           int limit, uint64_t &left, int &rest)
+                                           int limit, uint64_t &left, int &rest, int *took)
 {
     const int lane = threadIdx.x & 63;
     const int leaf0 = tr.leaf0();
@@ -217,7 +224,7 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
                 in = 0;
             } else {
                 if (all) {
-                    if (run.done && !capped && r - l >= kLongRange) {
+                    if (run.ctrl && !capped && r - l >= kLongRange) {
                         leave();
                         break;
                     }
@@ -267,12 +274,15 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
         }
         if (sp == 0) break;
         // time to leave the rest of the queries that have one to other waves?
-        if (run.done && !capped && steps >= next_look) {
+        if (run.ctrl && !capped && steps >= next_look) {
             next_look = steps + kLookEvery;
             bool stop = run.waves <= (uint32_t)kDrainWaves || steps >= kLongWalk;
-            if (!stop)
-                stop = (int)(run.waves - kSample * __hip_atomic_load(run.done, __ATOMIC_RELAXED,
-                                                                     __HIP_MEMORY_SCOPE_AGENT)) <= kDrainWaves;
+            if (!stop) {
+                const uint32_t done = __hip_atomic_load(&run.ctrl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint32_t sum = __hip_atomic_load(&run.ctrl->steps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                stop = (int)(run.waves - kSample * done) <= kDrainWaves &&
+                       (steps >= kLongCall || (uint64_t)steps * done >= (uint64_t)kLongFor * kStepUnit * sum);
+            }
             if (stop) {
                 in = 0;
                 leave();
@@ -293,6 +303,7 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
         wave_sync();
     }
     wave_sync();   // the packet's LDS is free again
+    if (took) *took = steps;
     return cnt;
 }
 
@@ -302,20 +313,21 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
 template <class Q, bool FILL>
 __device__ __forceinline__ int packet(const Tree &tr, const PacketRun &run, const Q &q, bool whole, bool mine,
                                       PacketLds<Q> &lds, int32_t *__restrict__ out, int64_t at, int limit,
-                                      uint64_t &left, int &rest)
+                                      uint64_t &left, int &rest, int *took = nullptr)
 {
     if (ballot(whole && !q.plain()) == 0) {
-        if (tr.points) return packet_walk<Q, typename Q::PlainPoint, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest);
-        return packet_walk<Q, typename Q::Plain, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest);
+        if (tr.points) return packet_walk<Q, typename Q::PlainPoint, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took);
+        return packet_walk<Q, typename Q::Plain, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took);
     }
-    return packet_walk<Q, Q, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest);
+    return packet_walk<Q, Q, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took);
 }
 
 // ------------------------------------------------------------ light walks
 //
 // Every query walks from the root in a packet.  The first kHitCache hits of
 // a query are kept for the fill call.  A packet is heavy once it has taken
-// `patience` steps while the machine runs dry, or kLongWalk, or when it meets
+// `patience` steps, and far more than others, while the machine runs dry, or
+// kLongWalk, or when it meets
 // a node of more than kLongRange leaves that one of its queries contains:
 // then it stops in front of its next node, and the rest, the leaves from
 // that node's first one on, is cut into tasks.  The machine runs dry when no
@@ -365,13 +377,13 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
     if (mine) q.load(queries, j);
     PacketRun run{};
     run.l = -1;
-    run.done = &ctrl->done;
+    run.ctrl = ctrl;
     run.waves = gridDim.x;
     run.patience = patience;
     uint64_t left;
-    int rest;
+    int rest, steps;
     const int cnt = packet<Q, false>(tr, run, q, mine, mine, lds, cache, (int64_t)(mine ? j : 0) * kHitCache,
-                                     kHitCache, left, rest);
+                                     kHitCache, left, rest, &steps);
     if (mine) {
         light[j] = cnt;
         counts[j] = cnt;
@@ -384,7 +396,10 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
             h.packet = (int)p;
             heavy[atomicAdd(&ctrl->heavy, 1u)] = h;
         }
-        if (blockIdx.x / 8 % kSample == 0 && gridDim.x > (unsigned)kDrainWaves) atomicAdd(&ctrl->done, 1u);
+        if (blockIdx.x / 8 % kSample == 0 && gridDim.x > (unsigned)kDrainWaves) {
+            atomicAdd(&ctrl->steps, (uint32_t)(steps < 4096 ? steps : 4096) / kStepUnit);
+            atomicAdd(&ctrl->done, 1u);
+        }
     }
 }
 

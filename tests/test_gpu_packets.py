@@ -134,3 +134,24 @@ def test_pool_of_tasks_runs_out(ws):
     q[:, 2], q[:, 5] = z - 0.001, z + 0.001
     hits = _check(tree, ref, q, 1, ws)
     assert hits > 500 * m
+
+
+@pytest.mark.parametrize("m", [(1 << 18) - 1, 1 << 18, (1 << 18) + 8193])
+@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18])
+def test_query_sort_tile_and_tree_size_lines(n, m, ws):
+    """Both sides of the query count where the order's sort takes larger
+    tiles (and the scan several rounds of look-back), and of the tree size
+    where packets wait longer before they leave their rest."""
+    rng = np.random.default_rng([59, n, m])
+    p = rng.random((n, 3), dtype=np.float32)
+    p[: n // 8] = p[: n // 8] * np.float32(0.01) + np.float32(0.5)     # a dense corner
+    q = workloads.spheres(rng.random((m, 3), dtype=np.float32), np.float32(0.004))
+    q[::9, :3] = np.float32(0.505)
+    q[:: m // 40, 3] = np.float32(0.06)                                # a few far longer walks
+    ref = oracle.build(0, p, 30)
+    tree, _ = gpu_build(p, 0, 30, ws)
+    oracle.threads(16)
+    try:
+        assert _check(tree, ref, q, 0, ws) > m
+    finally:
+        oracle.threads(1)
