@@ -798,11 +798,12 @@ KNOBS = ("sort_variant32", "sort_variant64", "batch_sort_variant", "query_split1
          "batch_sort_mode", "radix_mode")
 
 KERNEL_GROUPS = {  # rocprofv3 kernel-name fragment -> bench kernel name (first match wins)
-    "k_onesweep<unsigned int, 512, 4>": "query_order", "k_qorder": "query_order",
+    "k_onesweep<unsigned int, 512, 4": "query_order", "k_onesweep<unsigned int, 1024, 8, 8>": "query_order",
+    "k_qorder": "query_order",
     "k_bounds<": "bounds", "k_bounds_final": "bounds_final", "k_morton": "morton",
     "k_onesweep": "sort_pass", "k_bottomup_l0": "bottomup", "k_bottomup_up": "bottomup_up",
-    "k_split": "query_split", "k_leaf_scan_count": "query_count", "k_leaf_count_wide": "query_count",
-    "k_leaf_mixed_count": "query_count", "k_leaf_fill": "query_fill", "copyBuffer": "copy",
+    "k_query_reset": "query_split", "k_walk": "query_count", "k_cut": "query_count", "k_task": "query_count",
+    "k_scan": "scan", "k_fill": "query_fill", "copyBuffer": "copy",
     "k_batch_plan": "batch_plan", "k_batch_morton": "morton", "k_batch_count": "query_count",
     "k_batch_fill": "query_fill", "k_scene_sort": "scene_sort", "k_ray_first": "ray_first",
     "k_radix_count": "sort_count",

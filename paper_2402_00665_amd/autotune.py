@@ -32,12 +32,11 @@ KNOB_CANDIDATES = {
     "radix_mode": [0, 1],
     "radix_bits64": [8, 9, 11],
 }
-# (query_split1, query_split2, query_leaf_mode, query_order): each split
-# schedule with the queries as given and in Morton order
-# Coarse blocks suit thin queries (rays, segments), whose hits fall in few
-# Morton ranges but whose finer pieces would exceed the split levels'
-# capacity; (24, 24): blocks larger than the tree, each query one plain
-# Alg. 1 walk by one lane.
+# (query_split1, query_split2, query_leaf_mode, query_order): each schedule
+# with the queries as the library orders them and in Morton order in any
+# case.  split1 and leaf_mode set the leaves of a task, split2 the steps a
+# packet walks before it may leave its rest to tasks; (24, 24): packets are
+# hardly ever cut.
 _SPLITS = [(12, 7, 0), (13, 8, 0), (12, 8, 0), (12, 6, 0), (13, 7, 0), (11, 6, 0),
            (12, 7, 1), (11, 6, 1), (13, 7, 1), (11, 5, 1), (14, 10, 1), (16, 10, 1),
            (14, 9, 1), (15, 10, 0), (24, 24, 0)]
