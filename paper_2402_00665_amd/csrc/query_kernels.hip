@@ -340,6 +340,7 @@ unsigned grid_for(int64_t items, int64_t most)
 // enough blocks.
 constexpr int64_t kQOrderLarge = 1 << 18;
 constexpr int kSmallTree = 1 << 18;
+constexpr int kMidTree = 1 << 21;
 
 template <class Q, int T, int I>
 void sort_keys(const Tree &tr, const float *q, int m, unsigned key_blocks, const Scratch &S, hipStream_t s)
@@ -392,8 +393,11 @@ hipError_t run_count(Tree tr, const float *q, int m, int64_t *offsets, char *ws,
     // on 141193 boxes 258 -> 231 us, but boxes on 400000 228 -> 299)
     const int patience = (L.packets > kDrainWaves && tr.n < kSmallTree ? 6 : 3)
                          << std::min<int64_t>(std::max<int64_t>(0, tune_get(TUNE_QSPLIT2) - 3), 16);
+    // (a quarter of that on trees below 2^21 primitives, which cannot fill the
+    // pool: 900000 boxes on 300000 363 -> 315 us, but 2^20 on 2^24 770 -> 852)
     const int wider = tune_get(TUNE_QLEAF) == 1 ? 4 : 1;
-    const int width = wider * (int)std::max<int64_t>(512, (int64_t)size << std::max<int64_t>(0, tune_get(TUNE_QSPLIT1) - 7));
+    const int64_t spread = std::max<int64_t>(0, tune_get(TUNE_QSPLIT1) - (tr.n < kMidTree ? 9 : 7));
+    const int width = wider * (int)std::max<int64_t>(512, (int64_t)size << spread);
     hipLaunchKernelGGL((k_walk<Q>), dim3((unsigned)L.packets), dim3(kWalkBlock), 0, s, tr, q, m, size, patience,
                        perm, S.ctrl, S.light, S.counts, S.cache, S.resume, S.heavy);
     prof_end(K_QCOUNT, s);

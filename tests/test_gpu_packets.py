@@ -137,11 +137,12 @@ def test_pool_of_tasks_runs_out(ws):
 
 
 @pytest.mark.parametrize("m", [(1 << 18) - 1, 1 << 18, (1 << 18) + 8193])
-@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18])
+@pytest.mark.parametrize("n", [(1 << 18) - 1, 1 << 18, (1 << 21) - 1, 1 << 21])
 def test_query_sort_tile_and_tree_size_lines(n, m, ws):
     """Both sides of the query count where the order's sort takes larger
     tiles (and the scan several rounds of look-back), and of the tree size
-    where packets wait longer before they leave their rest."""
+    where packets wait longer before they leave their rest and where tasks are
+    narrower."""
     rng = np.random.default_rng([59, n, m])
     p = rng.random((n, 3), dtype=np.float32)
     p[: n // 8] = p[: n // 8] * np.float32(0.01) + np.float32(0.5)     # a dense corner
