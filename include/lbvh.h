@@ -396,9 +396,11 @@ const char *lbvh_last_hip_error(void);
  *       has at most 262144 primitives; larger batches run mode 0.
  *   "query_split1": the rest of a heavy packet of queries is cut into tasks of
  *       at most 2^(split1 - 7) leaves per query of the packet, at least 512;
- *       values 2 .. 24 (default 12: 2048 leaves for a packet of 64).
+ *       values 2 .. 24 (default 12: 2048 leaves for a packet of 64; a
+ *       quarter on trees of less than 2^21 primitives).
  *   "query_split2": how long a packet walks before its rest may be cut: about
- *       2^(split2 - 3) times 3 steps; values 2 .. 24 (default 7: 48).
+ *       2^(split2 - 3) times 3 steps; values 2 .. 24 (default 7: 48; twice
+ *       that where many queries meet a tree of less than 2^18 primitives).
  *   "query_leaf_mode": 0 = tasks of that width (default), 1 = four times wider.
  *   "query_order": 1 = the single-tree count call first sorts the queries
  *       by a 16-bit Morton key of their centres (in the root's box) and
