@@ -110,7 +110,8 @@ KERNEL_SOURCES = ["paper_2402_00665_amd/csrc/build_kernels.hip",
                   "paper_2402_00665_amd/csrc/device_common.hpp",
                   "paper_2402_00665_amd/csrc/lbvh_internal.hpp",
                   "paper_2402_00665_amd/csrc/scene_sort.hpp",
-                  "paper_2402_00665_amd/csrc/query_walk.hpp"]
+                  "paper_2402_00665_amd/csrc/query_walk.hpp",
+                  "paper_2402_00665_amd/csrc/task_pool.hpp"]
 
 
 def source_hash() -> str:

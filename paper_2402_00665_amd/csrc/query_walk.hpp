@@ -5,6 +5,7 @@
 #pragma clang fp contract(off)
 
 #include "query_common.hpp"
+#include "task_pool.hpp"
 
 namespace lbvh {
 namespace {
@@ -47,11 +48,12 @@ struct Task {
 struct QueryCtrl {   // the count call's control words, zeroed at its start
     uint32_t done;       // one in kSample of the waves whose light walks are finished
     uint32_t heavy;      // heavy packets
-    uint32_t tasks;      // tasks
+    unsigned long long tasks;   // tasks asked for
     uint32_t scan_tile;  // the scan's tile counter
     int32_t ordered;     // the queries were walked in the order `perm`
-    uint32_t own;        // some packet's tasks lie in places of its own
     uint32_t error;      // at kQueryErrorByte
+    uint32_t tasks_end;  // where the pool of tasks ends when more were asked for than it holds
+    uint32_t own;        // some packet's tasks lie in places of its own
     uint32_t sort_tile[2];
     uint32_t steps;      // of the waves that `done` counts, in units of kStepUnit
 };
@@ -411,12 +413,18 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
 // children, as far as any query passes them.  A list longer than a quarter of
 // `most` makes the width four times larger, one longer than half of it is
 // left as it is.  The list is then the packet's tasks in leaf order.  Where
-// the pool of tasks has no room for them, the packet is cut again, into at
-// most kOwnTasks tasks that have places of their own.
+// the pool of tasks has no room for them (reserve_places), the packet is cut
+// again, into at most kOwnTasks tasks that have places of their own.
 constexpr int kCutBlock = 512;  // (256 threads with lists of 512: 1.9 ms on the box queries, not 0.8)
 constexpr int kCutWaves = kCutBlock / 64;
 constexpr int kCutList = 1024;   // list entries, and so the most tasks of a packet
 constexpr int kCutAhead = 4;    // nodes of a wave whose children are loaded together
+
+struct TaskCounter {
+    QueryCtrl *ctrl;
+    __device__ uint64_t add(uint32_t cnt) { return atomicAdd(&ctrl->tasks, (unsigned long long)cnt); }
+    __device__ void close(uint32_t end) { ctrl->tasks_end = end; }
+};
 
 struct CutList {
     int l[kCutList], r[kCutList], g[kCutList];
@@ -536,15 +544,10 @@ __global__ __launch_bounds__(kCutBlock) void k_cut(Tree tr, const float *__restr
             first = (int64_t)max_tasks + h * kOwnTasks;
             break;
         }
-        // (an add that does not fit leaves the counter past the end until it
-        // is taken back, so no other fits meanwhile: the tasks have no gaps)
         if (tid == 0) {
-            s_first = cnt > 0 ? atomicAdd(&ctrl->tasks, (uint32_t)cnt) : 0u;
-            s_fits = s_first <= max_tasks && max_tasks - s_first >= (uint32_t)cnt;
-            if (!s_fits) {
-                atomicSub(&ctrl->tasks, (uint32_t)cnt);
-                ctrl->own = 1u;
-            }
+            s_first = 0u;
+            s_fits = cnt == 0 || reserve_places(TaskCounter{ctrl}, (uint32_t)cnt, max_tasks, &s_first);
+            if (!s_fits) ctrl->own = 1u;
         }
         __syncthreads();
         first = s_first;
@@ -567,7 +570,8 @@ template <class F>
 __device__ __forceinline__ void each_task(const QueryCtrl *ctrl, uint32_t max_tasks, const HeavyPacket *heavy,
                                           const Task *tasks, F &&f)
 {
-    const int64_t T = ctrl->tasks, own = ctrl->own ? (int64_t)ctrl->heavy * kOwnTasks : 0;
+    const int64_t T = places_given(ctrl->tasks, ctrl->tasks_end, max_tasks);
+    const int64_t own = ctrl->own ? (int64_t)ctrl->heavy * kOwnTasks : 0;
     for (int64_t k = blockIdx.x; k < T + own; k += gridDim.x) {
         int64_t t = k;
         if (k >= T) {

@@ -156,3 +156,25 @@ def test_query_sort_tile_and_tree_size_lines(n, m, ws):
         assert _check(tree, ref, q, 0, ws) > m
     finally:
         oracle.threads(1)
+
+
+def test_pool_of_tasks_runs_out_unevenly(ws):
+    """Queries whose rests make from a few to many hundred tasks, in turn,
+    more than the pool holds: some packets are refused while smaller ones
+    still fit."""
+    rng = np.random.default_rng(89)
+    n, m = 1 << 20, 1000
+    p = rng.random((n, 3), dtype=np.float32)
+    ref = oracle.build(0, p, 30)
+    tree, _ = gpu_build(p, 0, 30, ws)
+    c = rng.random((m, 3))
+    half = np.empty((m, 3))
+    half[0::4] = [2.0, 2.0, 0.0005]      # slabs
+    half[1::4] = [2.0, 0.004, 0.004]     # columns
+    half[2::4] = [0.03, 0.03, 0.03]
+    half[3::4] = [2.0, 0.3, 0.0005]      # strips
+    half[8::64] = [0.4, 0.4, 0.0005]
+    q = np.concatenate([c - half, c + half], 1).astype(np.float32)
+    for _ in range(3):
+        hits = _check(tree, ref, q, 1, ws)
+    assert hits > 200 * m
