@@ -411,7 +411,9 @@ const char *lbvh_last_hip_error(void);
  *       in the workspace, and the fill call follows that whatever the knob
  *       is when it is enqueued.
  *   "query_walk_budget": for tests of the error path: caps the node visits
- *       of each walk of a count call (0 = no cap beyond 2n, the default).
+ *       of each walk of a count call, a packet's where queries walk together
+ *       (0 = no cap beyond 2n, the default, which also ends a walk on nodes
+ *       that are no tree).
  *       A walk that hits the cap stops; lbvh_query_check then reports it.
  *   "morton_order": 1 = the single-tree build's Morton-code kernel sweeps
  *       the primitives from the end of the array to its start, the

@@ -227,7 +227,7 @@ struct Tree {
     const int32_t *perm;   // leaf k -> primitive
     int n;
     uint32_t *err = nullptr;   // count calls: where a walk that ran out of budget is flagged
-    int64_t budget = 0;        // node visits allowed per walk; 0: 2n (every node once)
+    int64_t budget = 0;        // node visits allowed per walk (a packet's, for range queries); 0: 2n
     bool points = false;       // a tree of points: every leaf box has hi == lo
     __device__ int64_t walk_budget() const { return budget > 0 ? budget : 2 * (int64_t)n; }
     // a walk stopped with its budget spent: its count is short; report it

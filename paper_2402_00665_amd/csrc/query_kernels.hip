@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_first(Tree tr, const float *_
                 }
                 r = s.x < s.y ? s.y : s.x;
             }
-            if (--budget < 0 && go) {
+            if ((--budget < 0 || sp >= kRayDepth) && go) {   // (also where the nodes are no tree)
                 tr.budget_spent();
                 go = false;
             }

@@ -150,7 +150,7 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
     if (mine) reinterpret_cast<T *>(lds.queries)[lane] = t;
     wave_sync();
     const bool capped = !FILL && tr.budget > 0;
-    int64_t budget = tr.budget;
+    int budget = (int)tr.walk_budget();   // 2n, at most 2^31 - 4, or the knob's
     int cnt = 0, steps = 0, sp = 0, next_look = run.patience;
     bool off = !mine;      // this lane's query has stopped
     left = 0;
@@ -202,7 +202,9 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
     };
     while (true) {
         if (in != 0) {
-            if (capped && --budget < 0) {
+            // (the nodes of a tree are met once each, at most kPacketDepth of
+            // them waiting: this ends a walk on nodes that are no tree)
+            if ((--budget | (kPacketDepth - 1 - sp)) < 0) {
                 if (lane == 0) tr.budget_spent();
                 break;
             }
@@ -468,7 +470,9 @@ __global__ __launch_bounds__(kCutBlock) void k_cut(Tree tr, const float *__restr
             a.all[0] = 0;
         }
         __syncthreads();
-        while (cnt > 0 && cnt <= most / 2) {
+        // (no path has kPacketDepth nodes: that ends the loop on nodes that are
+        // no tree, whose tasks' walks then report it)
+        for (int level = 0; cnt > 0 && cnt <= most / 2 && level < kPacketDepth; ++level) {
             if (cnt > most / 4) width *= 4;
             bool grew = false;
             for (int e0 = wv * kCutAhead; e0 < cnt; e0 += kCutWaves * kCutAhead) {
