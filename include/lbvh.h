@@ -234,14 +234,17 @@ int lbvh_query_rays_fill(const lbvh_tree *tree, const float *rays, int64_t m,
 
 /* First hit of each ray: among the primitives it matches, the one with the
  * smallest entry parameter, ties to the smallest Morton-order position.
- * One pruned Alg. 1 walk per ray: a node is entered only if the ray meets
- * its box with an entry parameter below the best hit so far (a box inside
+ * One walk per ray from the root, the nearer child first: a node is entered
+ * only if the ray meets its box with an entry parameter below the best hit
+ * so far, or equal to it and with leaves before the best hit's (a box inside
  * another never has a smaller entry parameter, so nothing is lost).
  *   hit       : device int32 [m]: input index of the primitive, -1 if none.
  *   t         : device float [m]: its entry parameter, +inf if none.
  *   workspace : device, at least lbvh_query_workspace_bytes(m) bytes,
- *               256-byte aligned; only its error word is used, and
- *               lbvh_query_check reads it as after a count call.
+ *               256-byte aligned.  The call uses its error word, which
+ *               lbvh_query_check reads as after a count call, and a part that
+ *               no other call uses: what a count call of m queries left there
+ *               stays good for its fill.
  * m = 0 enqueues nothing. */
 int lbvh_query_rays_first(const lbvh_tree *tree, const float *rays, int64_t m,
                           int32_t *hit, float *t, void *workspace,

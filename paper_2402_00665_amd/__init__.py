@@ -448,7 +448,8 @@ def query_first(tree: Tree, rays, workspace: Workspace | None = None, hit=None, 
                 stream=None):
     """First hit of each ray (float32 CUDA [m, 8] = o.xyz, tmin, d.xyz,
     tmax): (hit int32 [m], input index or -1; t float32 [m], entry
-    parameter or +inf) on the device; asynchronous."""
+    parameter or +inf) on the device; asynchronous.  What a count call of
+    as many queries left in the workspace stays good for its fill."""
     torch = _torch()
     q = _dev_f32(rays, 8, "rays")
     m = int(q.shape[0])

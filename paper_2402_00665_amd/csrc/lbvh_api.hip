@@ -62,10 +62,9 @@ QueryLayout query_layout(int64_t m)
     L.rows = take(tasks * L.packet * sizeof(int32_t));
     L.places = take(tasks * L.packet * sizeof(int32_t));
     L.scan_status = take((mm / kScanTile + 1) * sizeof(uint64_t));
-    L.deep = 0;
-    const size_t share = (size_t)ray_share(m), deep_lanes = (mm + share - 1) / share * ray_lanes((int)share);
-    off = std::max(off, align256(deep_lanes * (kRayDepth - kRayStack) * 8));
     L.ctrl = take(128);
+    const size_t share = (size_t)ray_share(m), deep_lanes = (mm + share - 1) / share * ray_lanes((int)share);
+    L.deep = take(deep_lanes * (kRayDepth - kRayStack) * 8);
     L.total = off;
     // the query-order sort's buffers live in `cache`, which is first
     // written by the walks, after the sort is done with them (for few

@@ -141,8 +141,10 @@ struct QueryLayout {
     size_t qhist;      // 2 x kRadix uint32
     size_t scan_status; // scan tiles uint64 (batched too)
     size_t hcache;     // batched: m x 64 int32, each query's first hits
-    size_t deep;       // first hits: the walks' deep stacks, in place of all of the above
     size_t ctrl;       // control words (batched too)
+    // the first-hit call has the error word and this alone, so that a count
+    // call's state outlives it
+    size_t deep;       // the walks' deep stacks
     size_t total;
 };
 

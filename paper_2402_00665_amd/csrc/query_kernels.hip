@@ -474,7 +474,7 @@ hipError_t launch_ray_first(const lbvh_node *nodes, int n, const float *rays, in
     const Scratch S = carve(ws, L);
     Tree tr{reinterpret_cast<const float4 *>(nodes), nullptr, n, &S.ctrl->error, tune_get(TUNE_QBUDGET)};
     prof_begin(K_QCOUNT, s);
-    hipLaunchKernelGGL(k_query_reset, dim3(1), dim3(kBlock), 0, s, S.ctrl, 0, S.scan_status, (int64_t)0, S.qhist);
+    hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(kBlock), 0, s, (int64_t *)nullptr, (int64_t)0, &S.ctrl->error);
     const int share = ray_share(m);
     const int64_t waves = ((int64_t)m + share - 1) / share;
     hipLaunchKernelGGL(k_ray_first, dim3((unsigned)waves), dim3(kRayBlock), 0, s, tr, rays, m, share, hit,

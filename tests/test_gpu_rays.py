@@ -247,3 +247,35 @@ def test_first_hit_rays_per_wave(n, m, ws):
     rhit, rt, _ = oracle.ray_first_traverse(rays, ref)
     hit, t = gpu_first(tree, rays, ws)
     assert_first_equal(hit, t, rhit, rt)
+
+
+@pytest.mark.parametrize("n,m", [(3000, 700), (200000, 2000), (100000, 40000)])
+def test_first_hit_between_count_and_fill(n, m):
+    """A first-hit call on the workspace of a count call, of as many rays or
+    other queries, leaves the count's state for its fill: kept hits, walks
+    again, tasks, and (40000) the order; and its own answers stay exact, with
+    stacks deeper than the entries kept on chip."""
+    import torch
+    import paper_2402_00665_amd as lb
+    rng = np.random.default_rng([101, n])
+    boxes = workloads.clustered_boxes(n, rng, components=5, sigma=0.02)
+    rays = workloads.rays_toward((boxes[rng.integers(0, n, m), :3]), rng)
+    ref = oracle.build(1, boxes, 30)
+    tree, _ = gpu_build(boxes, 1, 30)
+    rhit, rt, _ = oracle.ray_first_traverse(rays, ref)
+    c = (boxes[rng.integers(0, n, m), :3]).astype(np.float64)
+    s = np.where(np.arange(m)[:, None] % 50 == 0, 0.05, 0.001) * np.ones((m, 3))
+    qws = lb.Workspace()
+    dr = torch.from_numpy(rays).cuda()
+    for qkind, q in ((1, np.concatenate([c - s, c + s], 1).astype(np.float32)), (RAYS, rays)):
+        roff, ridx, _ = oracle.query_traverse(qkind, q, ref)
+        dq = torch.from_numpy(q).cuda()
+        say(f"  count, first hit, fill: qkind {qkind}, {int(roff[-1])} hits")
+        off = lb.query_count(tree, dq, qkind, qws)
+        hit, t = lb.query_first(tree, dr, workspace=qws)
+        lb.check_query(qws, m)
+        idx = torch.empty(int(off[-1].item()), dtype=torch.int32, device="cuda")
+        lb.query_fill(tree, dq, qkind, idx, qws)
+        torch.cuda.synchronize()
+        assert_query_equal(off.cpu().numpy(), idx.cpu().numpy(), roff, ridx)
+        assert_first_equal(hit.cpu().numpy(), t.cpu().numpy(), rhit, rt)
