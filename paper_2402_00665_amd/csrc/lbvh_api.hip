@@ -39,7 +39,7 @@ BuildLayout build_layout(int64_t n, int code_bits)
     return L;
 }
 
-QueryLayout query_layout(int64_t m)
+static QueryLayout query_areas(int64_t m)
 {
     QueryLayout L{};
     size_t off = 0;
@@ -78,6 +78,18 @@ QueryLayout query_layout(int64_t m)
     L.qstatus[0] = inner(qtiles * kRadix * sizeof(uint32_t));
     L.qstatus[1] = inner(qtiles * kRadix * sizeof(uint32_t));
     L.qhist = inner((size_t)kQOrderPasses * kRadix * sizeof(uint32_t));
+    return L;
+}
+
+// A workspace for m queries is large enough for fewer: where a packet takes
+// more queries, or a wave more rays, the areas together shrink, and the size
+// before that is kept.  (The sizes at the ends of the rays' shares rise.)
+QueryLayout query_layout(int64_t m)
+{
+    QueryLayout L = query_areas(m);
+    constexpr int64_t kShareStep = kRayBlock * kRayWaves;
+    for (const int64_t last : {(int64_t)kQOrderMin - 1, m / kShareStep * kShareStep - 1})
+        if (0 <= last && last < m) L.total = std::max(L.total, query_areas(last).total);
     return L;
 }
 
