@@ -376,9 +376,10 @@ const char *lbvh_last_hip_error(void);
  *   "radix_bits32", "radix_bits64": digit width of the radix sort (single
  *       and batched builds) for 30-bit / 63-bit codes: 8 or 10 bits
  *       (4 or 3 passes; default 8) and 8, 9 or 11 bits (8, 7 or 6 passes;
- *       default 9).  Other values are refused.  A width and a tile shape
- *       that both stand at their defaults let the build choose both by its
- *       size (for a batch: while its mode stands at its default too).
+ *       default 9).  Other values are refused.
+ *   "sort_by_size": 1 = a digit width and a tile shape that both stand at
+ *       their defaults let the build choose both by its size (a batch: width,
+ *       shape and mode; default); 0 = every build is sorted as the knobs say.
  *   "sort_variant32", "sort_variant64": tile shape of the radix passes for
  *       30-bit / 63-bit codes: 0 = 256 threads x 16 keys, 1 = 256 x 8,
  *       2 = 256 x 24, 3 = 512 x 8, 4 = 512 x 16, 5 = 1024 x 8, 6 = 768 x 16,
@@ -389,8 +390,7 @@ const char *lbvh_last_hip_error(void);
  *       radix passes: 0 = 256 x 16 (default), 1 = 256 x 8, 2 = 512 x 8,
  *       3 = 512 x 16 (1 runs as 0 with 11-bit digits).
  *   "batch_sort_mode": how the batched build sorts: 0 = segmented radix
- *       passes over all scenes (default; with shape and width at their
- *       defaults: chosen by the batch's sizes), 1 = one block per scene, which
+ *       passes over all scenes (default; see "sort_by_size"), 1 = one block per scene, which
  *       computes the scene's box and codes and runs every pass over the
  *       scene itself (no look-back between blocks); in this mode
  *       "batch_sort_variant" picks the block: 0 = 256 x 16, 1 = 512 x 8,

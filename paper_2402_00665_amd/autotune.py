@@ -127,7 +127,8 @@ def tune(prims, code_bits: int, kind: int | None = None, seg_off=None, max_scene
     """Tune the radix digit width and tile shape for this workload (a single
     tree, or a batch when ``seg_off`` is given), and for a single tree the
     pass form ("radix_mode"): each candidate is timed as the codes kernel
-    plus all radix passes of a build.  Returns {"knobs": {knob: value},
+    plus all radix passes of a build (the knobs' defaults as the library runs
+    them: by size, while "sort_by_size" is on).  Returns {"knobs": {knob: value},
     "times_ms": {"bits/shape[/mode]": ms per build}}; every candidate is
     checked to give the same tree, bit for bit, as the first (current) one."""
     import torch

@@ -301,7 +301,8 @@ constexpr BatchSortShape kBatchShapes[] = {{256, 16}, {256, 8}, {512, 8}, {512, 
 
 // How a batch of N primitives in scenes of at most max_scene is sorted: one
 // block per scene or segmented passes, digit width, shape.  The knobs' choice,
-// unless mode, shape and width stand at their defaults.  Then one block per
+// unless "sort_by_size" is on and mode, shape and width stand at their
+// defaults.  Then one block per
 // scene where it sorts a scene on chip (up to a tile of 4096 or 8192), or where
 // there are so many scenes that the largest block, alone with max_scene keys, is not
 // what takes the time (us of whole 63-bit builds, block against segmented:
@@ -320,8 +321,7 @@ BatchPlan batch_plan(int64_t N, int64_t max_scene, int levels, int code_bits)
     // upper level: kChunk * kFanout primitives); a block alone on a scene of
     // millions would set the whole batch's time
     const bool can = levels <= 1;
-    if (tune_is_default(TUNE_BATCH_SORT_MODE) && tune_is_default(TUNE_BATCH_SORT) &&
-        tune_is_default(short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64)) {
+    if (sort_by_size({TUNE_BATCH_SORT_MODE, TUNE_BATCH_SORT, short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64})) {
         const bool many = N >= 128 * max_scene;
         if (can && (max_scene <= 8192 || many))
             return {true, short_codes ? 8 : 9, max_scene > (many ? 65536 : 4096) ? 2 : 1};

@@ -166,7 +166,7 @@ constexpr size_t sort_lds_bytes(int key_bytes, int threads, int items, int bits)
 }
 
 // Digit width and tile shape of a build of n primitives: the knobs', unless
-// both stand at their defaults.  Then by size (whole builds of uniform points,
+// "sort_by_size" is on and both stand at their defaults.  Then by size (whole builds of uniform points,
 // us, against 8 bits in 512 x 16 and 9 bits in 768 x 16): small tiles while
 // they do not fill the 256 CUs, so that more blocks share the work, and the
 // largest for large builds, whose tiles then look back less often.
@@ -193,7 +193,7 @@ SortPlan sort_plan(int64_t n)
     constexpr bool short_codes = sizeof(K) == 4;
     constexpr int bits_knob = short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64;
     constexpr int shape_knob = short_codes ? TUNE_SORT_VARIANT32 : TUNE_SORT_VARIANT64;
-    if (tune_is_default(bits_knob) && tune_is_default(shape_knob)) {
+    if (sort_by_size({bits_knob, shape_knob})) {
         const int64_t round6 = 256 * 768 * 16, round7 = 256 * 1024 * 16;
         const int large = !short_codes && (n + round6 - 1) / round6 == (n + round7 - 1) / round7 ? 6 : 7;
         const int variant = n <= (short_codes ? 1 << 17 : 1 << 19) ? 3 : (n <= (1 << 21) ? 5 : large);

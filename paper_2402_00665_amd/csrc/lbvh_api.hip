@@ -144,22 +144,27 @@ BatchLayout batch_layout(int64_t N, int S, int64_t max_scene, int code_bits)
 // ---------------------------------------------------------------- tuning
 
 namespace {
-// a digit width and a tile shape that both stand at their defaults leave the
-// choice to the build (sort_plan, batch_plan)
+// with "sort_by_size" a digit width and a tile shape that both stand at their
+// defaults leave the choice to the build (sort_plan, batch_plan)
 std::atomic<int64_t> g_tune[TUNE_NUM] = {{4}, {6}, {0}, {kSplit1}, {kSplit2}, {0}, {0}, {8}, {9}, {0},
-                                         {1}, {0}, {0}};
-const int64_t kTuneDefault[TUNE_NUM] = {4, 6, 0, kSplit1, kSplit2, 0, 0, 8, 9, 0, 1, 0, 0};
+                                         {1}, {0}, {0}, {1}};
+const int64_t kTuneDefault[TUNE_NUM] = {4, 6, 0, kSplit1, kSplit2, 0, 0, 8, 9, 0, 1, 0, 0, 1};
 const char *kTuneNames[TUNE_NUM] = {"sort_variant32", "sort_variant64", "batch_sort_variant",
                                     "query_split1", "query_split2", "query_leaf_mode",
                                     "query_order", "radix_bits32", "radix_bits64",
                                     "query_walk_budget", "morton_order", "batch_sort_mode",
-                                    "radix_mode"};
-const int64_t kTuneMin[TUNE_NUM] = {0, 0, 0, 2, 2, 0, 0, 8, 8, 0, 0, 0, 0};   // accepted values: min .. max
-const int64_t kTuneMax[TUNE_NUM] = {8, 8, 3, 24, 24, 1, 1, 10, 11, INT32_MAX, 1, 1, 1};
+                                    "radix_mode", "sort_by_size"};
+const int64_t kTuneMin[TUNE_NUM] = {0, 0, 0, 2, 2, 0, 0, 8, 8, 0, 0, 0, 0, 0};   // accepted values: min .. max
+const int64_t kTuneMax[TUNE_NUM] = {8, 8, 3, 24, 24, 1, 1, 10, 11, INT32_MAX, 1, 1, 1, 1};
 }  // namespace
 
 int64_t tune_get(int knob) { return g_tune[knob].load(std::memory_order_relaxed); }
-bool tune_is_default(int knob) { return tune_get(knob) == kTuneDefault[knob]; }
+bool sort_by_size(std::initializer_list<int> knobs)
+{
+    bool all = tune_get(TUNE_SORT_BY_SIZE) != 0;
+    for (const int k : knobs) all = all && tune_get(k) == kTuneDefault[k];
+    return all;
+}
 
 int radix_bits(int code_bits)
 {

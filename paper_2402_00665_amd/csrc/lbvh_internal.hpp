@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <initializer_list>
 
 #include "lbvh.h"
 
@@ -195,11 +196,11 @@ int batch_levels(int64_t max_scene);
 enum TuneKnob {
     TUNE_SORT_VARIANT32 = 0, TUNE_SORT_VARIANT64, TUNE_BATCH_SORT, TUNE_QSPLIT1, TUNE_QSPLIT2, TUNE_QLEAF, TUNE_QORDER,
     TUNE_RADIX_BITS32, TUNE_RADIX_BITS64, TUNE_QBUDGET, TUNE_MORTON_ORDER, TUNE_BATCH_SORT_MODE,
-    TUNE_RADIX_MODE,
+    TUNE_RADIX_MODE, TUNE_SORT_BY_SIZE,
     TUNE_NUM
 };
 int64_t tune_get(int knob);
-bool tune_is_default(int knob);
+bool sort_by_size(std::initializer_list<int> knobs);   // the knob is on, and these stand at their defaults
 
 // ------------------------------------------------------------ timing
 
