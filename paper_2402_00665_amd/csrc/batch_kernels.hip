@@ -299,22 +299,32 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(const float4 *__restrict_
 struct BatchSortShape { int threads, items; };
 constexpr BatchSortShape kBatchShapes[] = {{256, 16}, {256, 8}, {512, 8}, {512, 16}};
 
-// How a batch of N primitives in scenes of at most max_scene is sorted: one
+// How a batch of N primitives in S scenes of at most max_scene is sorted: one
 // block per scene or segmented passes, digit width, shape.  The knobs' choice,
 // unless "sort_by_size" is on and mode, shape and width stand at their
-// defaults.  Then one block per
-// scene where it sorts a scene on chip (up to a tile of 4096 or 8192), or where
-// there are so many scenes that the largest block, alone with max_scene keys, is not
-// what takes the time (us of whole 63-bit builds, block against segmented:
-// 64 scenes up to 4000: 70 / 105, with their queries 83 up to 5569: 175 / 208,
-// 4096 up to 65536 (537 times the largest):
-// 2551 / 3942, 300 up to 250000 (157 times): 3854 / 4168, but 512 up to 65536
-// (55 times): 727 / 568).  Blocks of 512 x 8, or 1024 x 8 where scenes exceed
-// 65536, or 4096 and are few; segmented passes of 512 x 8 and 10 or 9 bits (568 against 596 us on
-// those 512 scenes with 256 x 16).
+// defaults.  Then (us of whole builds, points, 30-bit / 63-bit codes; scenes of
+// one size, or log-uniform from 32 up to it)
+//   one block per scene where it sorts a scene on chip (up to a tile of 4096 or
+//     8192 keys), however few or many scenes there are, against segmented
+//     passes of 512 x 8:
+//       1 of 2000  48 against 57 / 60 against 86,  1024  149, 203 / 177, 330
+//       1 of 8192  68, 73 / 93, 112,  128  114, 141 / 143, 220,  1024  435, 476 / 575, 765
+//     and where the batch holds 128 times its largest scene or more, whose
+//     block, alone with max_scene keys, is then not what takes the time:
+//       128 of 65536  605, 622 / 862, 877,  4000 up to 65536  1785, 2311 / 2305, 3560,
+//       but 700 up to 65536 (84 to 103 times)  555, 514 / 764, 668;
+//   blocks of 1024 x 8 where the largest scenes' blocks set the time, alone or
+//     nearly so on their CUs, else of 512 x 8, three to a CU:
+//       128 of 65536  605 against 735 / 862, 1002,  256  892, 1034 / 1164, 1329,
+//       260  1224, 1148 / 1717, 1532,  1400 up to 65536 (170 times)  692, 831 / 1014, 1223,
+//       up to 30000 (215 times)  426, 429 / 551, 563,  up to 20000  326, 305 / 444, 397;
+//     in both, 8-bit digits for 30-bit codes, as the tables of 10 bits cost
+//     more than their one pass less (128 of 65536  605 against 649; 1 of 2000  48, 46);
+//   segmented passes of 512 x 8 and 10 or 9 bits otherwise (512 scenes up to
+//     65536 568 against 596 with 256 x 16).
 struct BatchPlan { bool block; int bits, variant; };
 
-BatchPlan batch_plan(int64_t N, int64_t max_scene, int levels, int code_bits)
+BatchPlan batch_plan(int64_t N, int S, int64_t max_scene, int levels, int code_bits)
 {
     const bool short_codes = code_bits <= 32;
     // one block per scene only while every scene is small (at most one
@@ -323,8 +333,9 @@ BatchPlan batch_plan(int64_t N, int64_t max_scene, int levels, int code_bits)
     const bool can = levels <= 1;
     if (sort_by_size({TUNE_BATCH_SORT_MODE, TUNE_BATCH_SORT, short_codes ? TUNE_RADIX_BITS32 : TUNE_RADIX_BITS64})) {
         const bool many = N >= 128 * max_scene;
-        if (can && (max_scene <= 8192 || many))
-            return {true, short_codes ? 8 : 9, max_scene > (many ? 65536 : 4096) ? 2 : 1};
+        const bool wide = max_scene > 65536 || (max_scene > 24576 && N <= 256 * max_scene) ||
+                          (max_scene > 4096 && (!many || S <= 256));
+        if (can && (max_scene <= 8192 || many)) return {true, short_codes ? 8 : 9, wide ? 2 : 1};
         return {false, short_codes ? 10 : 9, 2};
     }
     const int bits = radix_bits(code_bits);
@@ -458,7 +469,7 @@ hipError_t run_batch(const float *prims, const int64_t *seg_off, int S, int64_t 
     Climb *pend[2] = {reinterpret_cast<Climb *>(ws + L.pend[0]), reinterpret_cast<Climb *>(ws + L.pend[1])};
     float4 *nodes = reinterpret_cast<float4 *>(nodes_);
 
-    const BatchPlan plan = batch_plan(N, max_scene, levels, code_bits);
+    const BatchPlan plan = batch_plan(N, S, max_scene, levels, code_bits);
     const int bits = plan.bits, variant = plan.variant;
     const int tile = kBatchShapes[variant].threads * kBatchShapes[variant].items;
     int32_t *order = reinterpret_cast<int32_t *>(ws + L.order);

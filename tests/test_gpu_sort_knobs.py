@@ -1,6 +1,7 @@
 """Sort knobs asked for at their default values ("sort_by_size" off) run as
-they say: the number of launches tells which form ran, and trees equal the
-oracle's bit for bit."""
+they say: the number of launches tells which form ran.  And batches on both
+sides of the lines between the blocks' shapes.  Trees equal the oracle's bit
+for bit."""
 
 import numpy as np
 import pytest
@@ -76,3 +77,17 @@ def test_segmented_full_size(by_size):
         assert got == 7
     finally:
         oracle.threads(1)
+
+
+@pytest.mark.parametrize("bits", [30, 63])
+@pytest.mark.parametrize("sizes", [
+    [4097] * 256, [4097] * 257,                          # a block a CU, and more
+    [24576] * 2 + [12300] * 254 + [24576], [24577] * 2 + [12300] * 256,
+    [24577] + [12300] * 512, [24577] + [12400] * 512,    # 256 times the largest, and above
+])
+def test_block_shape_lines(sizes, bits):
+    rng = np.random.default_rng([109, sum(sizes), bits])
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    p = rng.random((int(off[-1]), 3), dtype=np.float32)
+    p[: off[-1] // 4] = np.round(p[: off[-1] // 4] * 8) / 8   # many equal codes
+    batched_parity(p, off, bits, 0, check_every=max(1, len(sizes) // 40))
