@@ -61,6 +61,7 @@ static QueryLayout query_areas(int64_t m)
     L.tasks = take(tasks * 32);
     L.rows = take(tasks * L.packet * sizeof(int32_t));
     L.places = take(tasks * L.packet * sizeof(int32_t));
+    L.max_nodes = (uint32_t)std::min<size_t>((off - L.rows) / 32, 1 << 30);
     L.scan_status = take((mm / kScanTile + 1) * sizeof(uint64_t));
     L.ctrl = take(128);
     const size_t share = (size_t)ray_share(m), deep_lanes = (mm + share - 1) / share * ray_lanes((int)share);

@@ -135,6 +135,7 @@ struct QueryLayout {
     size_t tasks;      // (max_tasks + kOwnTasks packets) x 32 bytes
     size_t rows;       // (the same) x packet int32: hits of each task's queries
     size_t places;     // the same: their places among the queries' hits
+    uint32_t max_nodes; // nodes of 32 bytes that heavy packets may leave, in `rows` and `places`
     // the query order's radix sort, inside `cache` (unused until the walks)
     size_t qkeys[2];   // m uint32 each
     size_t qvals;      // m int32 (first pass's values)

@@ -299,7 +299,7 @@ struct Scratch {
     int32_t *light, *counts, *cache, *resume, *rows, *places, *perm, *qvals;
     int64_t *offsets;
     HeavyPacket *heavy;
-    Task *tasks;
+    Task *tasks, *nodes;
     uint64_t *scan_status;
     uint32_t *qkeys[2], *qstatus[2], *qhist;
 };
@@ -317,6 +317,7 @@ Scratch carve(char *ws, const QueryLayout &L)
     at(S.heavy, L.heavy);
     at(S.tasks, L.tasks);
     at(S.rows, L.rows);
+    at(S.nodes, L.rows);
     at(S.places, L.places);
     at(S.scan_status, L.scan_status);
     at(S.perm, L.perm);
@@ -399,11 +400,11 @@ hipError_t run_count(Tree tr, const float *q, int m, int64_t *offsets, char *ws,
     const int64_t spread = std::max<int64_t>(0, tune_get(TUNE_QSPLIT1) - (tr.n < kMidTree ? 9 : 7));
     const int width = wider * (int)std::max<int64_t>(512, (int64_t)size << spread);
     hipLaunchKernelGGL((k_walk<Q>), dim3((unsigned)L.packets), dim3(kWalkBlock), 0, s, tr, q, m, size, patience,
-                       perm, S.ctrl, S.light, S.counts, S.cache, S.resume, S.heavy);
+                       perm, S.ctrl, S.light, S.counts, S.cache, S.resume, S.heavy, S.nodes, L.max_nodes);
     prof_end(K_QCOUNT, s);
     prof_begin(K_QSPLIT, s);
     hipLaunchKernelGGL((k_cut<Q>), dim3((unsigned)std::min<int64_t>(L.packets, kCutGrid)), dim3(kCutBlock), 0, s, tr,
-                       q, m, size, width, perm, S.resume, S.ctrl, S.heavy, L.max_tasks, S.tasks);
+                       q, m, size, width, perm, S.resume, S.ctrl, S.heavy, L.max_tasks, S.tasks, S.nodes);
     prof_end(K_QSPLIT, s);
     prof_begin(K_QCOUNT, s);
     const unsigned gt = (unsigned)std::min<int64_t>((int64_t)L.max_tasks, kTaskGrid);

@@ -26,6 +26,12 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int lane)
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
 }
 
+__device__ __forceinline__ float4 readlane4(float4 v, int lane)
+{
+    auto get = [&](float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane)); };
+    return make_float4(get(v.x), get(v.y), get(v.z), get(v.w));
+}
+
 // ---------------------------------------------------------------- records
 
 // A packet that left the rest of its walk to others: its queries that have
@@ -34,7 +40,9 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int lane)
 struct HeavyPacket {
     uint64_t queries;
     int32_t packet, first, tasks;
-    int32_t unused[3];
+    int32_t nodes;        // of the rest, in leaf order, as the walk left them (0: no room for them)
+    uint32_t first_node;  // the first of them
+    int32_t unused;
 };
 
 // A node and the queries of the packet that walk it: passed its box, and of
@@ -47,17 +55,20 @@ struct Task {
 
 struct QueryCtrl {   // the count call's control words, zeroed at its start
     uint32_t done;       // one in kSample of the waves whose light walks are finished
-    uint32_t heavy;      // heavy packets
-    unsigned long long tasks;   // tasks asked for
     uint32_t scan_tile;  // the scan's tile counter
-    int32_t ordered;     // the queries were walked in the order `perm`
+    uint32_t nodes;      // nodes that heavy packets left, and
+    uint32_t heavy;      // heavy packets: one add moves both
+    unsigned long long tasks;   // tasks asked for
     uint32_t error;      // at kQueryErrorByte
+    int32_t ordered;     // the queries were walked in the order `perm`
     uint32_t tasks_end;  // where the pool of tasks ends when more were asked for than it holds
     uint32_t own;        // some packet's tasks lie in places of its own
     uint32_t sort_tile[2];
     uint32_t steps;      // of the waves that `done` counts, in units of kStepUnit
 };
 static_assert(offsetof(QueryCtrl, error) == kQueryErrorByte, "error word");
+static_assert(offsetof(QueryCtrl, nodes) % 8 == 0 && offsetof(QueryCtrl, heavy) == offsetof(QueryCtrl, nodes) + 4,
+              "one 64-bit word");
 
 // ------------------------------------------------------------ packet walk
 //
@@ -121,6 +132,13 @@ __device__ __forceinline__ void load_uniform(const float4 *nodes, int v, float4 
     b = make_float4(y.x, y.y, y.z, y.w);
 }
 
+// Where a packet walk stopped: the current node, if `in` is not zero, and so
+// many waiting nodes on the stack.
+struct PacketStop {
+    int l, r, g, waiting;
+    uint64_t in, all;
+};
+
 // What a packet walk covers.
 struct PacketRun {
     int l, r, g;              // the node it starts at: leaf range, split (l -1: the root)
@@ -141,7 +159,7 @@ struct PacketRun {
 template <class Q, class T, bool FILL>
 __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run, const Q &q, bool mine,
                                            PacketLds<Q> &lds, int32_t *__restrict__ out, int64_t out_at,
-                                           int limit, uint64_t &left, int &rest, int *took)
+                                           int limit, uint64_t &left, int &rest, int *took, PacketStop *stop_at)
 {
     const int lane = threadIdx.x & 63;
     const int leaf0 = tr.leaf0();
@@ -186,6 +204,7 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
             left |= mm;
         }
         left &= ballot(!off);
+        if (stop_at) *stop_at = PacketStop{l, r, g, sp, in, all};
     };
     // hits of query s, one bit per lane, whose leaf's primitive is prim
     auto report = [&](int s, uint64_t hits, int32_t prim) {
@@ -203,7 +222,9 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
     while (true) {
         if (in != 0) {
             // (the nodes of a tree are met once each, at most kPacketDepth of
-            // them waiting: this ends a walk on nodes that are no tree)
+            // them waiting: this ends a walk on nodes that are no tree; looked
+            // at behind the loads of the children, 2^20 spheres took 902
+            // instead of 888 us)
             if ((--budget | (kPacketDepth - 1 - sp)) < 0) {
                 if (lane == 0) tr.budget_spent();
                 break;
@@ -317,13 +338,13 @@ __device__ __forceinline__ int packet_walk(const Tree &tr, const PacketRun &run,
 template <class Q, bool FILL>
 __device__ __forceinline__ int packet(const Tree &tr, const PacketRun &run, const Q &q, bool whole, bool mine,
                                       PacketLds<Q> &lds, int32_t *__restrict__ out, int64_t at, int limit,
-                                      uint64_t &left, int &rest, int *took = nullptr)
+                                      uint64_t &left, int &rest, int *took = nullptr, PacketStop *stop_at = nullptr)
 {
     if (ballot(whole && !q.plain()) == 0) {
-        if (tr.points) return packet_walk<Q, typename Q::PlainPoint, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took);
-        return packet_walk<Q, typename Q::Plain, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took);
+        if (tr.points) return packet_walk<Q, typename Q::PlainPoint, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took, stop_at);
+        return packet_walk<Q, typename Q::Plain, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took, stop_at);
     }
-    return packet_walk<Q, Q, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took);
+    return packet_walk<Q, Q, FILL>(tr, run, q, mine, lds, out, at, limit, left, rest, took, stop_at);
 }
 
 // ------------------------------------------------------------ light walks
@@ -370,7 +391,8 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
                                                      int32_t *__restrict__ counts,
                                                      int32_t *__restrict__ cache,
                                                      int32_t *__restrict__ resume,
-                                                     HeavyPacket *__restrict__ heavy)
+                                                     HeavyPacket *__restrict__ heavy, Task *__restrict__ nodes,
+                                                     uint32_t max_nodes)
 {
     __shared__ PacketLds<Q> lds;
     const int lane = threadIdx.x;
@@ -386,20 +408,42 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
     run.patience = patience;
     uint64_t left;
     int rest, steps;
+    PacketStop stop;
     const int cnt = packet<Q, false>(tr, run, q, mine, mine, lds, cache, (int64_t)(mine ? j : 0) * kHitCache,
-                                     kHitCache, left, rest, &steps);
+                                     kHitCache, left, rest, &steps, &stop);
     if (mine) {
         light[j] = cnt;
         counts[j] = cnt;
         if ((left >> lane) & 1) resume[j] = rest;
     }
-    if (lane == 0) {
-        if (left) {
+    if (left) {
+        // the nodes of its rest, in leaf order, for the cut to start from
+        // (fewer than 2^25 packets of at most 97 nodes: no carry)
+        const int here = stop.in != 0;
+        unsigned long long was = 0;
+        if (lane == 0)
+            was = atomicAdd(reinterpret_cast<unsigned long long *>(&ctrl->nodes),
+                            (1ull << 32) | (uint32_t)(here + stop.waiting));
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)was);
+        const bool room = at <= max_nodes && (uint32_t)(here + stop.waiting) <= max_nodes - at;
+        if (room) {
+            if (here && lane == 0) nodes[at] = Task{stop.l, stop.r, stop.g, (int)p, stop.in, stop.all};
+            for (int k = lane; k < stop.waiting; k += 64) {
+                const int4 rg = lds.range[stop.waiting - 1 - k], mk = lds.masks[stop.waiting - 1 - k];
+                nodes[at + here + k] = Task{rg.x, rg.y, rg.z, (int)p, ((uint64_t)(uint32_t)mk.y << 32) | (uint32_t)mk.x,
+                                            ((uint64_t)(uint32_t)mk.w << 32) | (uint32_t)mk.z};
+            }
+        }
+        if (lane == 0) {
             HeavyPacket h{};
             h.queries = left;
             h.packet = (int)p;
-            heavy[atomicAdd(&ctrl->heavy, 1u)] = h;
+            h.nodes = room ? here + stop.waiting : 0;
+            h.first_node = at;
+            heavy[was >> 32] = h;
         }
+    }
+    if (lane == 0) {
         if (blockIdx.x / 8 % kSample == 0 && gridDim.x > (unsigned)kDrainWaves) {
             atomicAdd(&ctrl->steps, (uint32_t)(steps < 4096 ? steps : 4096) / kStepUnit);
             atomicAdd(&ctrl->done, 1u);
@@ -411,16 +455,28 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
 //
 // One block cuts the rest of one heavy packet into tasks, level by level: an
 // ordered list of nodes (range, split, queries that passed its box and that
-// contain it), each wave replacing nodes of more than `width` leaves by their
-// children, as far as any query passes them.  A list longer than a quarter of
-// `most` makes the width four times larger, one longer than half of it is
-// left as it is.  The list is then the packet's tasks in leaf order.  Where
-// the pool of tasks has no room for them (reserve_places), the packet is cut
-// again, into at most kOwnTasks tasks that have places of their own.
+// contain it), first those that the packet's walk left waiting, in which the
+// nodes of more than `width` leaves are replaced by their children, as far as
+// any query passes them.  A list longer than a quarter of `most` makes the
+// width four times larger, one longer than half of it is left as it is.  The
+// list is then the packet's tasks in leaf order.  Where the pool of tasks has
+// no room for them (reserve_places), the packet is cut again from the root,
+// into at most kOwnTasks tasks that have places of their own.
+//
+// Bound by the chain of levels, each at least a load's latency, of the packet
+// with the longest one.  A lane holds a node and loads its children, so that a
+// level loads once; a wave then takes its nodes to cut in turn, each lane
+// testing its query.  While they are few, one wave works alone, without
+// barriers (alone up to 2 or 4 cut nodes 31 and 26 us, up to 8 or 16 21).  On
+// 150000 boxes of side 0.002 over 10^6 clustered boxes, and on 2^20 over 2^24:
+// 21 and 63 us; from the root, each wave loading four nodes at a time, 58 and
+// 126; so from the waiting nodes, 43 and 153.
 constexpr int kCutBlock = 512;  // (256 threads with lists of 512: 1.9 ms on the box queries, not 0.8)
 constexpr int kCutWaves = kCutBlock / 64;
 constexpr int kCutList = 1024;   // list entries, and so the most tasks of a packet
-constexpr int kCutAhead = 4;    // nodes of a wave whose children are loaded together
+constexpr int kCutAlone = 32;    // nodes up to which one wave works alone,
+constexpr int kCutFew = 8;       // ... while so many of them are cut
+static_assert(kCutList == 2 * kCutBlock, "a thread for each node of a list that is cut");
 
 struct TaskCounter {
     QueryCtrl *ctrl;
@@ -428,24 +484,75 @@ struct TaskCounter {
     __device__ void close(uint32_t end) { ctrl->tasks_end = end; }
 };
 
+struct CutNode {
+    int l, r, g;
+    uint64_t in, all;
+};
+
 struct CutList {
     int l[kCutList], r[kCutList], g[kCutList];
     uint64_t in[kCutList], all[kCutList];
+    __device__ void put(int at, const CutNode &x)
+    {
+        l[at] = x.l;
+        r[at] = x.r;
+        g[at] = x.g;
+        in[at] = x.in;
+        all[at] = x.all;
+    }
+    __device__ CutNode get(int at) const { return CutNode{l[at], r[at], g[at], in[at], all[at]}; }
 };
 
+// Cuts the nodes of the lanes in `cuts`: x becomes the left child and y the
+// right one, with the queries of the wave that pass them.
 template <class Q>
-__global__ __launch_bounds__(kCutBlock) void k_cut(Tree tr, const float *__restrict__ queries, int m,
-                                                   int packet_size, int least_width,
-                                                   const int32_t *__restrict__ perm,
-                                                   const int32_t *__restrict__ resume, QueryCtrl *ctrl,
-                                                   HeavyPacket *__restrict__ heavy, uint32_t max_tasks,
-                                                   Task *__restrict__ tasks)
+__device__ __forceinline__ void cut_nodes(const Tree &tr, const Q &q, int from, uint64_t cuts, CutNode &x, CutNode &y)
 {
-    __shared__ CutList a, b;   // b: the children of a's nodes, two places each
-    __shared__ uint32_t s_sum[kCutWaves], s_first;
-    __shared__ bool s_fits;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int lane = threadIdx.x & 63;
     const int leaf0 = tr.leaf0();
+    const bool mine = (cuts >> lane) & 1;
+    float4 la{}, lb{}, ra{}, rb{};
+    if (mine) {
+        tr.load(x.g == x.l ? leaf0 + x.g : x.g, la, lb);
+        tr.load(x.g + 1 == x.r ? leaf0 + x.r : x.g + 1, ra, rb);
+    }
+    const CutNode node = x;
+    if (mine) {
+        x = CutNode{node.l, node.g, tr.index(__float_as_int(la.w)), 0, 0};
+        y = CutNode{node.g + 1, node.r, tr.index(__float_as_int(ra.w)), 0, 0};
+    }
+    for (uint64_t todo = cuts; todo; todo &= todo - 1) {
+        const int s = __ffsll((unsigned long long)todo) - 1;
+        const int l = __builtin_amdgcn_readlane(node.l, s), r = __builtin_amdgcn_readlane(node.r, s);
+        const int g = __builtin_amdgcn_readlane(node.g, s);
+        const uint64_t in = (uint64_t)readlane64((int64_t)node.in, s);
+        const float4 a = readlane4(la, s), b = readlane4(lb, s), c = readlane4(ra, s), d = readlane4(rb, s);
+        const uint64_t ml = ballot(q.test(a, b) && g >= from) & in;
+        const uint64_t mr = ballot(q.test(c, d) && r >= from) & in;
+        const uint64_t al = g - l >= kLeaves ? ballot(q.contains(a, b)) & ml : 0ull;
+        const uint64_t ar = r - g > kLeaves ? ballot(q.contains(c, d)) & mr : 0ull;
+        if (lane == s) {
+            x.in = ml;
+            x.all = al;
+            y.in = mr;
+            y.all = ar;
+        }
+    }
+}
+
+template <class Q>
+__global__ __launch_bounds__(kCutBlock, 4) void k_cut(Tree tr, const float *__restrict__ queries, int m,
+                                                      int packet_size, int least_width,
+                                                      const int32_t *__restrict__ perm,
+                                                      const int32_t *__restrict__ resume, QueryCtrl *ctrl,
+                                                      HeavyPacket *__restrict__ heavy, uint32_t max_tasks,
+                                                      Task *__restrict__ tasks, const Task *__restrict__ nodes)
+{
+    __shared__ CutList a, b;   // b: the parts of a's nodes, two places each
+    __shared__ uint32_t s_sum[kCutWaves], s_first;
+    __shared__ int s_cnt, s_level;
+    __shared__ bool s_fits, s_more;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n_heavy = ctrl->heavy;
     for (int64_t h = blockIdx.x; h < n_heavy; h += gridDim.x) {
         const uint64_t who = heavy[h].queries;
@@ -460,104 +567,90 @@ __global__ __launch_bounds__(kCutBlock) void k_cut(Tree tr, const float *__restr
         int cnt, most = kCutList;
         int64_t first;
         while (true) {
-        cnt = 1;
-        int64_t width = least_width;
-        if (tid == 0) {
-            a.l[0] = 0;
-            a.r[0] = tr.n - 1;
-            a.g[0] = tr.index(__float_as_int(tr.nodes[0].w));
-            a.in[0] = who;
-            a.all[0] = 0;
-        }
-        __syncthreads();
-        // (no path has kPacketDepth nodes: that ends the loop on nodes that are
-        // no tree, whose tasks' walks then report it)
-        for (int level = 0; cnt > 0 && cnt <= most / 2 && level < kPacketDepth; ++level) {
-            if (cnt > most / 4) width *= 4;
-            bool grew = false;
-            for (int e0 = wv * kCutAhead; e0 < cnt; e0 += kCutWaves * kCutAhead) {
-                float4 la[kCutAhead], lb[kCutAhead], ra[kCutAhead], rb[kCutAhead];
-#pragma unroll
-                for (int u = 0; u < kCutAhead; ++u) {
-                    const int e = e0 + u < cnt ? e0 + u : e0;
-                    const int l = a.l[e], r = a.r[e], g = a.g[e];
-                    if ((int64_t)r - l >= width) {
-                        tr.load(g == l ? leaf0 + g : g, la[u], lb[u]);
-                        tr.load(g + 1 == r ? leaf0 + r : g + 1, ra[u], rb[u]);
-                    }
+            int64_t width = least_width;
+            auto wide = [&](const CutNode &x) { return (int64_t)x.r - x.l >= width; };
+            // (no path has kPacketDepth nodes: that ends the loops on nodes that
+            // are no tree, whose tasks' walks then report it)
+            if (wv == 0) {
+                int level = 0;
+                bool more = true;
+                cnt = most == kCutList ? heavy[h].nodes : 0;
+                for (int k = lane; k < cnt; k += 64) {
+                    const Task x = nodes[heavy[h].first_node + k];
+                    a.put(k, CutNode{x.l, x.r, x.g, x.in, x.all});
                 }
-#pragma unroll
-                for (int u = 0; u < kCutAhead; ++u) {
-                    const int e = e0 + u;
-                    if (e >= cnt) break;
-                    const int l = a.l[e], r = a.r[e], g = a.g[e];
-                    const uint64_t in = a.in[e];
-                    if ((int64_t)r - l < width) {
-                        if (lane == 0) {
-                            b.l[2 * e] = l;
-                            b.r[2 * e] = r;
-                            b.g[2 * e] = g;
-                            b.in[2 * e] = in;
-                            b.all[2 * e] = a.all[e];
-                            b.in[2 * e + 1] = 0;
-                        }
-                        continue;
-                    }
-                    grew = true;
-                    const uint64_t ml = ballot(q.test(la[u], lb[u]) && g >= from) & in;
-                    const uint64_t mr = ballot(q.test(ra[u], rb[u]) && r >= from) & in;
-                    const uint64_t al = g - l >= kLeaves ? ballot(q.contains(la[u], lb[u])) & ml : 0ull;
-                    const uint64_t ar = r - g > kLeaves ? ballot(q.contains(ra[u], rb[u])) & mr : 0ull;
-                    if (lane < 2) {
-                        const bool left = lane == 0;
-                        b.l[2 * e + lane] = left ? l : g + 1;
-                        b.r[2 * e + lane] = left ? g : r;
-                        b.g[2 * e + lane] = tr.index(__float_as_int(left ? la[u].w : ra[u].w));
-                        b.in[2 * e + lane] = left ? ml : mr;
-                        b.all[2 * e + lane] = left ? al : ar;
-                    }
+                if (cnt == 0) {
+                    if (lane == 0) a.put(0, CutNode{0, tr.n - 1, tr.index(__float_as_int(tr.nodes[0].w)), who, 0});
+                    cnt = 1;
+                }
+                for (; cnt > 0 && cnt <= min(kCutAlone, most / 4) && level < kPacketDepth; ++level) {
+                    wave_sync();
+                    CutNode x = a.get(lane < cnt ? lane : 0), y{};
+                    wave_sync();
+                    const uint64_t cuts = ballot(lane < cnt && wide(x));
+                    more = cuts != 0;
+                    if (!more || __popcll(cuts) > kCutFew) break;
+                    if (lane >= cnt) x.in = 0;
+                    cut_nodes(tr, q, from, cuts, x, y);
+                    const uint64_t mx = ballot(x.in != 0), my = ballot(y.in != 0);
+                    const int at = (int)(lanes_below(mx) + lanes_below(my));
+                    if (x.in) a.put(at, x);
+                    if (y.in) a.put(at + (x.in ? 1 : 0), y);
+                    cnt = __popcll(mx) + __popcll(my);
+                }
+                if (lane == 0) {
+                    s_cnt = cnt;
+                    s_level = level;
+                    s_more = more;
                 }
             }
-            const bool more = __syncthreads_or(grew);
-            // the entries that have a query left, in order, back to a
-            int out = 0;
-            for (int c0 = 0; c0 < 2 * cnt; c0 += kCutBlock) {
-                const int e = c0 + tid;
-                const bool some = e < 2 * cnt && b.in[e] != 0;
-                const uint64_t mk = ballot(some);
-                if (lane == 0) s_sum[wv] = (uint32_t)__popcll(mk);
-                __syncthreads();
-                int at = out + (int)lanes_below(mk);
-                for (int w = 0; w < kCutWaves; ++w) {
-                    if (w < wv) at += s_sum[w];
-                    out += s_sum[w];
+            __syncthreads();
+            cnt = s_cnt;
+            for (int level = s_level; s_more && cnt > 0 && cnt <= most / 2 && level < kPacketDepth; ++level) {
+                if (cnt > most / 4) width *= 4;
+                const int e = lane * kCutWaves + wv;   // (neighbours, often cut together, in different waves)
+                CutNode x{}, y{};
+                if (e < cnt) x = a.get(e);
+                const uint64_t cuts = ballot(e < cnt && wide(x));
+                if (cuts) cut_nodes(tr, q, from, cuts, x, y);
+                if (e < cnt) {
+                    b.put(2 * e, x);
+                    b.put(2 * e + 1, y);
                 }
-                if (some) {
-                    a.l[at] = b.l[e];
-                    a.r[at] = b.r[e];
-                    a.g[at] = b.g[e];
-                    a.in[at] = b.in[e];
-                    a.all[at] = b.all[e];
+                const bool more = __syncthreads_or(cuts != 0);
+                // the parts that have a query left, in order, back to a
+                int out = 0;
+                for (int c0 = 0; c0 < 2 * cnt; c0 += kCutBlock) {
+                    const int k = c0 + tid;
+                    const bool some = k < 2 * cnt && b.in[k] != 0;
+                    const uint64_t mk = ballot(some);
+                    if (lane == 0) s_sum[wv] = (uint32_t)__popcll(mk);
+                    __syncthreads();
+                    int at = out + (int)lanes_below(mk);
+                    for (int w = 0; w < kCutWaves; ++w) {
+                        if (w < wv) at += s_sum[w];
+                        out += s_sum[w];
+                    }
+                    if (some) a.put(at, b.get(k));
+                    __syncthreads();
                 }
-                __syncthreads();
+                cnt = out;
+                if (!more) break;
             }
-            cnt = out;
-            if (!more) break;
-        }
-        if (most == kOwnTasks) {
-            first = (int64_t)max_tasks + h * kOwnTasks;
-            break;
-        }
-        if (tid == 0) {
-            s_first = 0u;
-            s_fits = cnt == 0 || reserve_places(TaskCounter{ctrl}, (uint32_t)cnt, max_tasks, &s_first);
-            if (!s_fits) ctrl->own = 1u;
-        }
-        __syncthreads();
-        first = s_first;
-        if (s_fits) break;
-        most = kOwnTasks;
-        __syncthreads();
+            if (most == kOwnTasks) {
+                first = (int64_t)max_tasks + h * kOwnTasks;
+                break;
+            }
+            if (tid == 0) {
+                s_first = 0u;
+                s_fits = cnt == 0 || reserve_places(TaskCounter{ctrl}, (uint32_t)cnt, max_tasks, &s_first);
+                if (!s_fits) ctrl->own = 1u;
+            }
+            __syncthreads();
+            first = s_first;
+            if (s_fits) break;
+            most = kOwnTasks;
+            __syncthreads();
         }
         for (int e = tid; e < cnt; e += kCutBlock)
             tasks[first + e] = Task{a.l[e], a.r[e], a.g[e], number, a.in[e], a.all[e]};

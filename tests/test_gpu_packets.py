@@ -178,3 +178,28 @@ def test_pool_of_tasks_runs_out_unevenly(ws):
     for _ in range(3):
         hits = _check(tree, ref, q, 1, ws)
     assert hits > 200 * m
+
+
+def test_rest_left_at_a_contained_node(ws):
+    """20400 queries, thousands of which leave their rest at a large node they
+    contain, some nodes waiting: more tasks than the pool holds, so that
+    packets are cut from what their walk left or, into their own few places,
+    from the root."""
+    import torch
+    import paper_2402_00665_amd as lb
+    rng = np.random.default_rng(113)
+    n, k, times = 1 << 18, 24, 850
+    p = rng.random((n, 3), dtype=np.float32)
+    ref = oracle.build(0, p, 30)
+    tree, _ = gpu_build(p, 0, 30, ws)
+    c, half = rng.uniform(0.3, 0.7, (k, 3)), rng.uniform(0.2, 0.26, (k, 3))
+    q = np.concatenate([c - half, c + half], 1).astype(np.float32)
+    roff, ridx, _ = oracle.query_traverse(1, q, ref)
+    dq = torch.from_numpy(np.tile(q, (times, 1))).cuda()
+    off, idx = lb.query(tree, dq, 1, workspace=ws)
+    lb.check_query(ws, k * times)
+    counts = (off[1:] - off[:-1]).cpu().numpy().reshape(times, k)
+    assert np.array_equal(counts, np.tile(np.diff(roff), (times, 1)))
+    first = torch.from_numpy(ridx).cuda()
+    for rows in idx.reshape(times, -1).split(50):
+        assert bool((rows == first).all())
