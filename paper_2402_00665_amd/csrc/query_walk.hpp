@@ -26,6 +26,13 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int lane)
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
 }
 
+__device__ __forceinline__ int wave_max(int v)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off));
+    return v;
+}
+
 __device__ __forceinline__ float4 readlane4(float4 v, int lane)
 {
     auto get = [&](float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane)); };
@@ -457,7 +464,9 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
 // ordered list of nodes (range, split, queries that passed its box and that
 // contain it), first those that the packet's walk left waiting, in which the
 // nodes of more than `width` leaves are replaced by their children, as far as
-// any query passes them.  A list longer than a quarter of `most` makes the
+// any query passes them.  Once they are not few, a level cuts those that are not
+// much shorter than the longest: the parts of the short ones would fill the
+// list and leave it whole.  A list longer than a quarter of `most` makes the
 // width four times larger, one longer than half of it is left as it is.  The
 // list is then the packet's tasks in leaf order.  Where the pool of tasks has
 // no room for them (reserve_places), the packet is cut again from the root,
@@ -476,6 +485,7 @@ constexpr int kCutWaves = kCutBlock / 64;
 constexpr int kCutList = 1024;   // list entries, and so the most tasks of a packet
 constexpr int kCutAlone = 32;    // nodes up to which one wave works alone,
 constexpr int kCutFew = 8;       // ... while so many of them are cut
+constexpr int kCutFirst = 2;     // a level cuts the nodes of at least the longest one's share
 static_assert(kCutList == 2 * kCutBlock, "a thread for each node of a list that is cut");
 
 struct TaskCounter {
@@ -550,7 +560,7 @@ __global__ __launch_bounds__(kCutBlock, 4) void k_cut(Tree tr, const float *__re
 {
     __shared__ CutList a, b;   // b: the parts of a's nodes, two places each
     __shared__ uint32_t s_sum[kCutWaves], s_first;
-    __shared__ int s_cnt, s_level;
+    __shared__ int s_cnt, s_level, s_longest[2];   // the longest range of a's nodes, by the level's parity
     __shared__ bool s_fits, s_more;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n_heavy = ctrl->heavy;
@@ -568,7 +578,9 @@ __global__ __launch_bounds__(kCutBlock, 4) void k_cut(Tree tr, const float *__re
         int64_t first;
         while (true) {
             int64_t width = least_width;
-            auto wide = [&](const CutNode &x) { return (int64_t)x.r - x.l >= width; };
+            auto wide = [&](const CutNode &x, int longest) {
+                return (int64_t)x.r - x.l >= max(width, (int64_t)longest / kCutFirst);
+            };
             // (no path has kPacketDepth nodes: that ends the loops on nodes that
             // are no tree, whose tasks' walks then report it)
             if (wv == 0) {
@@ -587,7 +599,7 @@ __global__ __launch_bounds__(kCutBlock, 4) void k_cut(Tree tr, const float *__re
                     wave_sync();
                     CutNode x = a.get(lane < cnt ? lane : 0), y{};
                     wave_sync();
-                    const uint64_t cuts = ballot(lane < cnt && wide(x));
+                    const uint64_t cuts = ballot(lane < cnt && wide(x, 0));
                     more = cuts != 0;
                     if (!more || __popcll(cuts) > kCutFew) break;
                     if (lane >= cnt) x.in = 0;
@@ -598,10 +610,15 @@ __global__ __launch_bounds__(kCutBlock, 4) void k_cut(Tree tr, const float *__re
                     if (y.in) a.put(at + (x.in ? 1 : 0), y);
                     cnt = __popcll(mx) + __popcll(my);
                 }
+                wave_sync();
+                int longest = 0;
+                for (int k = lane; k < cnt; k += 64) longest = max(longest, a.r[k] - a.l[k]);
+                longest = wave_max(longest);
                 if (lane == 0) {
                     s_cnt = cnt;
                     s_level = level;
                     s_more = more;
+                    s_longest[level & 1] = longest;
                 }
             }
             __syncthreads();
@@ -611,7 +628,8 @@ __global__ __launch_bounds__(kCutBlock, 4) void k_cut(Tree tr, const float *__re
                 const int e = lane * kCutWaves + wv;   // (neighbours, often cut together, in different waves)
                 CutNode x{}, y{};
                 if (e < cnt) x = a.get(e);
-                const uint64_t cuts = ballot(e < cnt && wide(x));
+                const uint64_t cuts = ballot(e < cnt && wide(x, s_longest[level & 1]));
+                if (tid == 0) s_longest[(level & 1) ^ 1] = 0;
                 if (cuts) cut_nodes(tr, q, from, cuts, x, y);
                 if (e < cnt) {
                     b.put(2 * e, x);
@@ -631,7 +649,13 @@ __global__ __launch_bounds__(kCutBlock, 4) void k_cut(Tree tr, const float *__re
                         if (w < wv) at += s_sum[w];
                         out += s_sum[w];
                     }
-                    if (some) a.put(at, b.get(k));
+                    CutNode part{};
+                    if (some) {
+                        part = b.get(k);
+                        a.put(at, part);
+                    }
+                    const int longest = wave_max(part.r - part.l);
+                    if (lane == 0 && longest > 0) atomicMax(&s_longest[(level & 1) ^ 1], longest);
                     __syncthreads();
                 }
                 cnt = out;
