@@ -344,8 +344,9 @@ def main():
     P = 12 if w.kind == 0 else 24
     K = 4 if w.code_bits == 30 else 8
     d8 = (w.code_bits + 7) // 8
-    radix_bits = lb.lbvh_tune(f"radix_bits{32 if w.code_bits == 30 else 64}")
-    d = (w.code_bits + radix_bits - 1) // radix_bits
+    # the passes that ran (the width knob at its default leaves them to the size)
+    d = max(1, round(kernels["sort_pass"]["launches_per_step"])) if "sort_pass" in kernels else d8
+    radix_bits = -(-w.code_bits // d)
     bpp = build_bytes_per_prim(P, K, d)
     for name, b in bpp.items():
         if name in kernels:
@@ -801,12 +802,11 @@ KNOBS = ("sort_variant32", "sort_variant64", "batch_sort_variant", "query_split1
          "batch_sort_mode", "radix_mode")
 
 KERNEL_GROUPS = {  # rocprofv3 kernel-name fragment -> bench kernel name (first match wins)
-    "k_onesweep<unsigned int, 512, 4": "query_order", "k_onesweep<unsigned int, 1024, 8, 8>": "query_order",
-    "k_qorder": "query_order",
+    ", 8, true>": "query_order", "k_qorder": "query_order",   # (k_onesweep's sort of the query order)
     "k_bounds<": "bounds", "k_bounds_final": "bounds_final", "k_morton": "morton",
     "k_onesweep": "sort_pass", "k_bottomup_l0": "bottomup", "k_bottomup_up": "bottomup_up",
-    "k_query_reset": "query_split", "k_walk": "query_count", "k_cut": "query_count", "k_task": "query_count",
-    "k_scan": "scan", "k_fill": "query_fill", "copyBuffer": "copy",
+    "k_query_reset": "query_split", "k_walk": "query_count", "k_cut": "query_split",
+    "k_task_count": "query_count", "k_task_places": "scan", "k_scan": "scan", "k_fill": "query_fill", "copyBuffer": "copy",
     "k_batch_plan": "batch_plan", "k_batch_morton": "morton", "k_batch_count": "query_count",
     "k_batch_fill": "query_fill", "k_scene_sort": "scene_sort", "k_ray_first": "ray_first",
     "k_radix_count": "sort_count",

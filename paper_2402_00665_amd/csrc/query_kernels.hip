@@ -350,10 +350,10 @@ void sort_keys(const Tree &tr, const float *q, int m, unsigned key_blocks, const
     hipLaunchKernelGGL((k_qorder_keys<Q>), dim3(key_blocks), dim3(kBlock), 0, s, tr, q, m, S.qkeys[0], S.qhist,
                        S.qstatus[0], (int64_t)tiles * kRadix);
     const SortSegs one{nullptr, nullptr, 1, 0};
-    hipLaunchKernelGGL((k_onesweep<uint32_t, T, I, kRadixBits>), dim3(tiles), dim3(T), 0, s, S.qkeys[0],
+    hipLaunchKernelGGL((k_onesweep<uint32_t, T, I, kRadixBits, true>), dim3(tiles), dim3(T), 0, s, S.qkeys[0],
                        S.qkeys[1], nullptr, S.qvals, (int64_t)m, one, 0, kRadixBits, S.qhist, S.qstatus[0],
                        S.qstatus[1], tiles, S.ctrl->sort_tile, tr.err, (const uint32_t *)nullptr);
-    hipLaunchKernelGGL((k_onesweep<uint32_t, T, I, kRadixBits>), dim3(tiles), dim3(T), 0, s, S.qkeys[1],
+    hipLaunchKernelGGL((k_onesweep<uint32_t, T, I, kRadixBits, true>), dim3(tiles), dim3(T), 0, s, S.qkeys[1],
                        S.qkeys[0], S.qvals, S.perm, (int64_t)m, one, kRadixBits, kRadixBits, S.qhist + kRadix,
                        S.qstatus[1], nullptr, 0u, S.ctrl->sort_tile + 1, tr.err, (const uint32_t *)nullptr);
 }

@@ -264,7 +264,8 @@ __global__ __launch_bounds__(kCountThreads) void k_radix_count(
 // form): block b is tile b and takes its digits' output positions from
 // toff[b] instead of the look-back; `next_rows` rows of `status_next` are
 // cleared (by the tiles of those numbers) for the next pass either way.
-template <typename K, int THREADS, int ITEMS, int BITS>
+// QUERIES names the sort of the query order, which profiles tell apart by it.
+template <typename K, int THREADS, int ITEMS, int BITS, bool QUERIES = false>
 __global__ __launch_bounds__(THREADS) void k_onesweep(
     const K *__restrict__ keys_in, K *__restrict__ keys_out, const int32_t *__restrict__ vals_in,
     int32_t *__restrict__ vals_out, int64_t n, SortSegs seg, int shift, int nbits,
