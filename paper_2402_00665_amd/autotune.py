@@ -1,7 +1,7 @@
 """Self-written autotuner for the library's launch-shape knobs.
 
 A knob (see ``lbvh_tune`` in include/lbvh.h) picks a digit width, a tile
-shape or a query piece size; results never depend on it, only speed does.
+shape or a schedule of the query walks; results never depend on it, only speed does.
 ``tune`` (radix digit width and tile shape of a build) and ``tune_query``
 (the query schedule) time every candidate on the caller's own workload with
 HIP events,

@@ -160,12 +160,10 @@ __global__ __launch_bounds__(kSceneThreads) void k_batch_morton(
     for (int64_t w = w0 + threadIdx.x; w < w1; w += kSceneThreads) status0[w] = 0u;
 }
 
-// Alg. 1 for query j on the tree of its scene (no splitting: batched
+// Alg. 1 for query j on the tree of its scene (one thread per query: batched
 // workloads have many scenes and light queries).  Containment reports whole
-// leaf ranges from leaf_perm, as in the single-tree leaf walk.
-// Alg. 1 for query j on the tree of its scene (one thread per query); the
-// fill pass writes through a HitStage (the block's queries have consecutive
-// output ranges).
+// leaf ranges from leaf_perm, as in the single-tree walks; the fill pass writes
+// through a HitStage (the block's queries have consecutive output ranges).
 // The batched count keeps each query's first kBatchHitCache hits (scenes
 // are small, so most queries have fewer); the fill copies them instead of
 // walking again.

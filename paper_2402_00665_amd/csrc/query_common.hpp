@@ -1,6 +1,6 @@
 // Query-side device code shared by the single-tree and batched query
-// translation units: the two predicates (with their containment tests), the
-// tree walker, the split and leaf-walk kernels and the CSR scan.
+// translation units: the predicates (with their containment tests), the tree,
+// the staged output of the batched fill and the CSR scan.
 #pragma once
 #pragma clang fp contract(off)
 
@@ -179,8 +179,7 @@ struct Ray {
     // forgoes a shortcut.
     __device__ bool contains(float4, float4) const { return false; }
     // the start point as a degenerate box: it keys the query order by where
-    // the ray starts, and makes the mixed leaf schedule walk (not scan) a
-    // ray's pieces
+    // the ray starts
     __device__ void bounds(float lo[3], float hi[3]) const
     {
 #pragma unroll
@@ -258,15 +257,6 @@ struct Tree {
         const int r = __float_as_int(b.w);
         return r == -1 ? n - 1 : index(r) - 1;
     }
-    // largest node whose range starts at leaf r (r <= n-1)
-    __device__ int first_at(int r) const
-    {
-        if (r <= n - 2) {
-            const int l = __float_as_int(nodes[2 * (int64_t)r].w);
-            if (index(l) >= r) return r;   // internal r is a right child
-        }
-        return n - 1 + r;
-    }
 };
 
 constexpr int kWavesPerBlock = kBlock / 64;
@@ -278,16 +268,16 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// Staged output of a fill pass, per wave.  The 64 items (pieces or
-// queries) a wave takes at a time have consecutive output ranges (item
-// order is output order), so the wave gathers their hits in its own LDS
+// Staged output of a fill pass, per wave.  The 64 queries a wave takes at a
+// time have consecutive output ranges (query order is output order), so the
+// wave gathers their hits in its own LDS
 // region and writes them out in one coalesced run:
-//   1. each lane walks its item; a leaf hit goes to the stage at its offset
+//   1. each lane walks its query; a leaf hit goes to the stage at its offset
 //      from the wave's first output slot (put), an all-hit leaf range
 //      becomes a job: output slot, first leaf_perm entry, length;
 //   2. the wave copies the jobs from leaf_perm, 64 entries per lane step,
 //      with up to kCopyDepth independent loads per lane in flight (a dense
-//      query's pieces are mostly such ranges: copying them one dependent
+//      query's hits are mostly such ranges: copying them one dependent
 //      load at a time is what made filling slower than counting);
 //   3. the wave writes the stage to the output.
 // Hits past the stage capacity, and jobs past the job list, are written

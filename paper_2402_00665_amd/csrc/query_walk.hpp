@@ -359,15 +359,16 @@ __device__ __forceinline__ int packet(const Tree &tr, const PacketRun &run, cons
 // Every query walks from the root in a packet.  The first kHitCache hits of
 // a query are kept for the fill call.  A packet is heavy once it has taken
 // `patience` steps, and far more than others, while the machine runs dry, or
-// kLongWalk, or when it meets
-// a node of more than kLongRange leaves that one of its queries contains:
-// then it stops in front of its next node, and the rest, the leaves from
-// that node's first one on, is cut into tasks.  The machine runs dry when no
+// kLongWalk, or when it meets a node of more than kLongRange leaves that one of
+// its queries contains: then it stops in front of its next node, and the rest,
+// the leaves from that node's first one on, is cut into tasks, from that node
+// and those that wait on its stack (kept where `rows` and `places` will be).  The machine runs dry when no
 // more than kDrainWaves of the launch's waves are still walking: until then
 // other waves fill the gaps of a long walk, and cutting it up would only
 // cost.  Where a walk stops depends on timing, the hits and their order do
 // not: a query's hits are those of its light walk followed by those of its
 // packet's tasks in leaf order.
+
 // The packet that block b of `blocks` takes.  Blocks go round the 8 XCDs one
 // by one; each XCD gets runs of kPacketRun neighbouring packets, which read
 // many of the same nodes, so that its L2 holds them.
@@ -478,14 +479,18 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk(Tree tr, const float *__res
 // testing its query.  While they are few, one wave works alone, without
 // barriers (alone up to 2 or 4 cut nodes 31 and 26 us, up to 8 or 16 21).  On
 // 150000 boxes of side 0.002 over 10^6 clustered boxes, and on 2^20 over 2^24:
-// 21 and 63 us; from the root, each wave loading four nodes at a time, 58 and
-// 126; so from the waiting nodes, 43 and 153.
+// 21 and 82 us; from the root, each wave loading four nodes at a time, 58 and
+// 126; so from the waiting nodes, 43 and 153.  Cutting all nodes at each level
+// took 63 us for the latter, but left ranges of millions of leaves whole where
+// the list filled up: 100 spheres of side 0.1 on 2^24 boxes 1334 us (now 253).
 constexpr int kCutBlock = 512;  // (256 threads with lists of 512: 1.9 ms on the box queries, not 0.8)
 constexpr int kCutWaves = kCutBlock / 64;
 constexpr int kCutList = 1024;   // list entries, and so the most tasks of a packet
 constexpr int kCutAlone = 32;    // nodes up to which one wave works alone,
 constexpr int kCutFew = 8;       // ... while so many of them are cut
-constexpr int kCutFirst = 2;     // a level cuts the nodes of at least the longest one's share
+// a level cuts the nodes of at least this share of the longest one's length
+// (2000 boxes of side 0.1 on 2^24: 0.49 ms, a quarter 2.98, an eighth 5.64)
+constexpr int kCutFirst = 2;
 static_assert(kCutList == 2 * kCutBlock, "a thread for each node of a list that is cut");
 
 struct TaskCounter {
