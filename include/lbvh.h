@@ -165,7 +165,8 @@ int lbvh_build_noalloc(int32_t kind, const float *prims, int64_t n, int32_t code
 
 /* ------------------------------------------------------------- queries */
 
-/* Workspace bytes for the count and fill calls over m queries. */
+/* Workspace bytes for the count, fill and first-hit calls over m queries; never
+ * less than for fewer queries. */
 int64_t lbvh_query_workspace_bytes(int64_t m);
 
 /* Range queries, first of two calls: Alg. 1 per query, counting hits.
